@@ -114,9 +114,9 @@ typedef struct {
 
 typedef struct ci_basis ci_basis; /* opaque */
 
-/* Launch shapes of the row passes (count, fill) and of the adjoint, kept in
+/* Launch shapes of the fill and of the adjoint, kept in
  * the handle.  Every shape computes the same result; only the time differs.
- * The row passes take one row per wavefront: either a grid that covers every
+ * The fill takes one row per wavefront: either a grid that covers every
  * row once (row_grab = 0), or a persistent grid (as many workgroups as the
  * device holds at once) whose wavefronts take row_grab consecutive rows at a
  * time from a work counter until none are left.  The adjoint gives each
@@ -127,7 +127,7 @@ typedef struct ci_basis ci_basis; /* opaque */
  * has its own tile fields, adjk_rows, adjk_tile_n and adjk_persistent, which
  * ci_hamiltonian_tune tunes when it is given room for the words. */
 typedef struct {
-    int32_t row_waves;      /* wavefronts per workgroup of count and fill: 4 or 8 */
+    int32_t row_waves;      /* wavefronts per workgroup of the fill: 4 or 8 */
     int32_t row_grab;       /* 0: one grid over all rows; 1..4096: persistent, rows per grab */
     int32_t adj_rows;       /* adjoint: target rows per tile, 1..4096 */
     int32_t adj_tile_n;     /* adjoint: neutron determinants per tile, 1..4096 */

@@ -230,44 +230,55 @@ __global__ void __launch_bounds__(256) partner_decode(PartnerArgs A, uint64_t* l
         glbw(A.self12)[x] = (int)(t - glb(A.l12_ptr)[x] - glb(A.seg12)[(int64_t)x * (A.nk + 1) + ky]);
 }
 
-// Per determinant x: segment counts -> segment offsets (exclusive scan over
-// the keys), list lengths into l*_ptr[x + 1].
+// Segment counts -> segment offsets (exclusive scan over the keys of each
+// determinant x), in both orders: seg[x][key], read by a wavefront that works
+// on one x, and segT[key][x], read by one that works on neighbouring x in one
+// key.  List lengths into l*_ptr[x + 1].  A workgroup takes kOffDets
+// determinants of one of the two lists, a wavefront a quarter of them, lanes
+// take keys; the transposed copy goes through LDS so that its stores are
+// contiguous too.
+constexpr int kOffDets = 32;
+
 __global__ void __launch_bounds__(64 * kPartnerWaves) partner_offsets(PartnerArgs A)
 {
-    const int lane = threadIdx.x & 63;
-    const int x = (int)blockIdx.x * kPartnerWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (x >= A.nsd) return;
-    const auto s1 = glbw(A.seg1 + (int64_t)x * (A.nk + 1));
-    const auto s12 = glbw(A.seg12 + (int64_t)x * (A.nk + 1));
-    int run1 = 0, run12 = 0;
-    for (int k0 = 0; k0 < A.nk; k0 += 64) {
-        const int k = k0 + lane;
-        const int a = k < A.nk ? s1[k] : 0, b = k < A.nk ? s12[k] : 0;
-        int ia = a, ib = b;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int ua = __shfl_up(ia, o, 64), ub = __shfl_up(ib, o, 64);
-            if (lane >= o) {
-                ia += ua;
-                ib += ub;
+    constexpr int kPer = kOffDets / kPartnerWaves;
+    __shared__ int32_t tile[kOffDets][65];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int xw = (int)blockIdx.x * kOffDets, x0 = xw + w * kPer;
+    const bool l12 = blockIdx.y != 0;
+    const auto seg = glbw(l12 ? A.seg12 : A.seg1), segT = glbw(l12 ? A.segT12 : A.segT1);
+    const auto ptr = glbw(l12 ? A.l12_ptr : A.l1_ptr);
+    const int nk = A.nk, nsd = A.nsd;
+    int run[kPer] = {};
+    for (int k0 = 0; k0 <= nk; k0 += 64) {
+        int c[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; i++)
+            c[i] = (x0 + i < nsd && k0 + lane < nk) ? seg[(int64_t)(x0 + i) * (nk + 1) + k0 + lane] : 0;
+#pragma unroll
+        for (int i = 0; i < kPer; i++) {
+            int incl = c[i];
+            for (int o = 1; o < 64; o <<= 1) {
+                const int u = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += u;
             }
+            const int off = run[i] + incl - c[i];
+            tile[w * kPer + i][lane] = off;
+            if (x0 + i < nsd && k0 + lane <= nk) seg[(int64_t)(x0 + i) * (nk + 1) + k0 + lane] = off;
+            run[i] += __shfl(incl, 63, 64);
         }
-        if (k < A.nk) {
-            s1[k] = run1 + ia - a;
-            s12[k] = run12 + ib - b;
+        __syncthreads();
+        const int m = nk + 1 - k0 < 64 ? nk + 1 - k0 : 64;
+        for (int t = threadIdx.x; t < m * kOffDets; t += 64 * kPartnerWaves) {
+            const int k = t / kOffDets, x = t % kOffDets;
+            if (xw + x < nsd) segT[(int64_t)(k0 + k) * nsd + xw + x] = tile[x][k];
         }
-        run1 += __shfl(ia, 63, 64);
-        run12 += __shfl(ib, 63, 64);
+        __syncthreads();
     }
-    if (lane == 0) {
-        s1[A.nk] = run1;
-        s12[A.nk] = run12;
-        glbw(A.l1_ptr)[x + 1] = run1;
-        glbw(A.l12_ptr)[x + 1] = run12;
-        if (x == 0) {  // so that the inclusive scan of l*_ptr gives offsets
-            glbw(A.l1_ptr)[0] = 0;
-            glbw(A.l12_ptr)[0] = 0;
-        }
-    }
+#pragma unroll
+    for (int i = 0; i < kPer; i++)
+        if (lane == 0 && x0 + i < nsd) ptr[x0 + i + 1] = run[i];
+    if (xw == 0 && threadIdx.x == 0) ptr[0] = 0;  // so that the inclusive scan of ptr gives offsets
 }
 
 }  // namespace
@@ -296,7 +307,8 @@ hipError_t launch_partner_count(const PartnerArgs& a, hipStream_t s)
 {
     if (a.nsd > 0) {
         launch_scan<false>(a, s);
-        hipLaunchKernelGGL(partner_offsets, dim3(grid_of(a.nsd)), dim3(64 * kPartnerWaves), 0, s, a);
+        hipLaunchKernelGGL(partner_offsets, dim3((unsigned)((a.nsd + kOffDets - 1) / kOffDets), 2),
+                           dim3(64 * kPartnerWaves), 0, s, a);
     } else {
         hipLaunchKernelGGL(partner_no_sd, dim3(1), dim3(1), 0, s, a);
     }

@@ -18,14 +18,13 @@
 #include "threebody.h"
 
 namespace ci {
-hipError_t launch_count(const BasisDev* bases, int nb, const int64_t* basis_row0, int64_t nrows,
-                        int64_t* row_ptr, int64_t nrp, const int64_t* seg_first, int64_t* scan_tmp,
-                        const ci_tuning& t, unsigned long long* queue, int full, hipStream_t s);
+hipError_t launch_count(const BasisDev* bases, int nb, const RowWork& w, int64_t* row_ptr, int64_t nrp,
+                        const int64_t* seg_first, int64_t* scan_tmp, int full, hipStream_t s);
 hipError_t launch_nnz(const int64_t* row_ptr, const int64_t* first, const int64_t* last, int64_t* nnz,
                       int n, hipStream_t s);
-hipError_t launch_fill(const BasisDev* bases, int nb, const int64_t* basis_row0, int64_t nrows,
-                       const float* tbme, const int64_t* row_ptr, int64_t nrp, int32_t* col, float* val,
-                       uint32_t* keys, const ci_tuning& t, unsigned long long* queue, int full, hipStream_t s);
+hipError_t launch_fill(const BasisDev* bases, const RowWork& w, const float* tbme, const int64_t* row_ptr, int64_t nrp,
+                       int32_t* col, float* val, uint32_t* keys, const ci_tuning& t, unsigned long long* queue, int full,
+                       hipStream_t s);
 hipError_t launch_vjp(const BasisDev* bases, int nbases, const int32_t* blk_basis, const int32_t* blk_local,
                       int nblocks, int64_t ntiles, int64_t* tile_off, AdjBasis* adjb, int64_t nbuckets, int chunks,
                       unsigned long long* part,
@@ -227,7 +226,7 @@ void fill_info(const HostBasis& hb, ci_basis_info& in)
 
 // offsets of one species' tables in the arena
 struct SpOff {
-    size_t sd, sdT, sd_key, key_off, key_nq, key_m2, l1_ptr, l12_ptr, seg1, seg12, self12;
+    size_t sd, sdT, sd_key, key_off, key_nq, key_m2, l1_ptr, l12_ptr, seg1, seg12, segT1, segT12, self12;
 };
 struct UOff {
     SpOff sp[2];
@@ -389,8 +388,8 @@ struct ci_basis {
     std::vector<size_t> lo1, lo12;                 // list offsets in the list memory
     std::vector<BasisDev> bd;                      // descriptors (list pointers set when placed)
     BasisDev* d_bases = nullptr;
-    int64_t* d_basis_row0 = nullptr;  // first global row of each basis, [n + 1]
     int64_t nrows = 0;                // sum of the dimensions
+    RowWork rows{};                   // how the row passes take the rows
     int64_t* d_seg_first = nullptr;   // R_b
     int64_t* d_seg_last = nullptr;    // R_b + D_b
     int64_t* d_scan_tmp = nullptr;
@@ -432,7 +431,7 @@ struct BuildPlan {
     std::vector<int> canon;
     std::vector<UOff> uo;
     size_t pair_start = 0, host_bytes = 0;
-    size_t o_row0 = 0, o_first = 0, o_last = 0, o_blk_basis = 0, o_blk_local = 0;
+    size_t o_row = 0, o_group = 0, o_first = 0, o_last = 0, o_blk_basis = 0, o_blk_local = 0;
     size_t o_bases = 0, o_scan = 0, o_nnz = 0, o_queue = 0, o_rec_count = 0, o_gscale = 0, o_tile_off = 0, o_adjb = 0;
     size_t bytes = 0;
     int nblocks = 0;
@@ -521,13 +520,14 @@ int plan_build(const ci_problem* probs, int32_t n_probs, BuildPlan& P, std::stri
         P.uo[u].orb_qn = L.take<int32_t>(hb.orb_n.size());
         ubytes[u] += L.off - s0;
     }
-    P.o_row0 = L.take<int64_t>(n_probs + 1);
     P.o_first = L.take<int64_t>(n_probs);
     P.o_last = L.take<int64_t>(n_probs);
     P.nblocks = 0;
     for (int32_t b = 0; b < n_probs; b++) P.nblocks += ub[P.which[b]]->nblk();
     P.o_blk_basis = L.take<int32_t>(std::max(P.nblocks, 1));
     P.o_blk_local = L.take<int32_t>(std::max(P.nblocks, 1));
+    P.o_row = L.take<int64_t>(P.nblocks + 1);
+    P.o_group = L.take<int64_t>(P.nblocks + 1);
     // the pair indices last: they are written after the partner kernels start
     P.pair_start = L.off;
     for (size_t u = 0; u < ub.size(); u++) {
@@ -552,6 +552,8 @@ int plan_build(const ci_problem* probs, int32_t n_probs, BuildPlan& P, std::stri
             o.l12_ptr = L.take<int64_t>(nsd + 1);
             o.seg1 = L.take<int32_t>(nsd * (nk + 1));
             o.seg12 = L.take<int32_t>(nsd * (nk + 1));
+            o.segT1 = L.take<int32_t>(nsd * (nk + 1));
+            o.segT12 = L.take<int32_t>(nsd * (nk + 1));
             o.self12 = L.take<int32_t>(nsd);
             ubytes[u] += L.off - s0;
             max_scan = std::max<int64_t>(max_scan, (int64_t)nsd + 1);
@@ -591,6 +593,8 @@ PartnerArgs partner_args(const ci_basis& h, size_t u, int sidx)
     a.l12_ptr = (int64_t*)(dev + o.l12_ptr);
     a.seg1 = (int32_t*)(dev + o.seg1);
     a.seg12 = (int32_t*)(dev + o.seg12);
+    a.segT1 = (int32_t*)(dev + o.segT1);
+    a.segT12 = (int32_t*)(dev + o.segT12);
     a.self12 = (int32_t*)(dev + o.self12);
     a.nsd = (int32_t)sp.nsd();
     a.nk = sp.nk();
@@ -745,26 +749,36 @@ int ci_basis_build(const ci_problem* probs, int32_t n_probs, ci_basis_info* info
                        ((hb.orb_m2[o] + 64) << 24);
         }
     }
-    std::vector<int64_t> first(n_probs), last(n_probs), row0(n_probs + 1, 0);
+    std::vector<int64_t> first(n_probs), last(n_probs);
     int64_t R = 0;
     for (int32_t b = 0; b < n_probs; b++) {
         const HostBasis& hb = *ub[P->which[b]];
         first[b] = R;
         last[b] = R + hb.dim;
-        row0[b + 1] = row0[b] + hb.dim;
         R += hb.dim + 1;
     }
     {
         int32_t* bb = (int32_t*)(mirror + P->o_blk_basis);
         int32_t* bl = (int32_t*)(mirror + P->o_blk_local);
+        int64_t* ro = (int64_t*)(mirror + P->o_row);
+        int64_t* go = (int64_t*)(mirror + P->o_group);
+        ro[0] = go[0] = 0;
         int gb = 0;
-        for (int32_t b = 0; b < n_probs; b++)
-            for (int k = 0; k < ub[P->which[b]]->nblk(); k++, gb++) {
+        for (int32_t b = 0; b < n_probs; b++) {
+            const HostBasis& hb = *ub[P->which[b]];
+            for (int k = 0; k < hb.nblk(); k++, gb++) {
                 bb[gb] = b;
                 bl[gb] = k;
+                const int64_t rows = hb.blk_off[k + 1] - hb.blk_off[k];
+                const int64_t nKn = hb.sp[1].key_off[hb.blk_kn[k] + 1] - hb.sp[1].key_off[hb.blk_kn[k]];
+                ro[gb + 1] = ro[gb] + rows;
+                go[gb + 1] = go[gb] + rows / nKn * ((nKn + kGroupRows - 1) / kGroupRows);
             }
+        }
+        h->rows = RowWork{(int32_t*)D(P->o_blk_basis), (int32_t*)D(P->o_blk_local), (int64_t*)D(P->o_row),
+                          (int64_t*)D(P->o_group), P->nblocks, ro[gb], go[gb]};
+        h->nrows = ro[gb];
     }
-    put(P->o_row0, row0.data(), row0.size() * 8);
     put(P->o_first, first.data(), first.size() * 8);
     put(P->o_last, last.data(), last.size() * 8);
     {
@@ -831,6 +845,8 @@ int ci_basis_build(const ci_problem* probs, int32_t n_probs, ci_basis_info* info
             sd.l12_ptr = (const int64_t*)D(o.l12_ptr);
             sd.seg1 = (const int32_t*)D(o.seg1);
             sd.seg12 = (const int32_t*)D(o.seg12);
+            sd.segT1 = (const int32_t*)D(o.segT1);
+            sd.segT12 = (const int32_t*)D(o.segT12);
             sd.self12 = (const int32_t*)D(o.self12);
             sd.nsd = (int32_t)hb.sp[sidx].nsd();
             sd.nk = hb.sp[sidx].nk();
@@ -867,7 +883,6 @@ int ci_basis_build(const ci_problem* probs, int32_t n_probs, ci_basis_info* info
         T += hb.n_tbme;
     }
     h->d_bases = (BasisDev*)D(P->o_bases);
-    h->d_basis_row0 = (int64_t*)D(P->o_row0);
     h->d_seg_first = (int64_t*)D(P->o_first);
     h->d_seg_last = (int64_t*)D(P->o_last);
     h->d_scan_tmp = scan_tmp;
@@ -882,7 +897,6 @@ int ci_basis_build(const ci_problem* probs, int32_t n_probs, ci_basis_info* info
     h->nblocks = P->nblocks;
     h->probs.assign(probs, probs + n_probs);
     h->tune = cached_tuning(h->probs);
-    h->nrows = row0[n_probs];
     h->n_rowptr = R;
     h->n_tbme = T;
     // the partner lists are still being counted on the stream
@@ -999,8 +1013,7 @@ static int count_impl(const ci_basis* b, int64_t* row_ptr, int64_t* nnz, int ful
     if (!b || !row_ptr || !nnz) return fail(CI_EINVAL, "null pointer");
     if (int rc = need_ready(b)) return rc;
     const int n = (int)b->info.size();
-    hipError_t e = launch_count(b->d_bases, n, b->d_basis_row0, b->nrows, row_ptr, b->n_rowptr, b->d_seg_first,
-                                b->d_scan_tmp, b->tune, b->d_queue, full, s);
+    hipError_t e = launch_count(b->d_bases, n, b->rows, row_ptr, b->n_rowptr, b->d_seg_first, b->d_scan_tmp, full, s);
     if (e != hipSuccess) return hip_fail(e, "count launch");
     e = launch_nnz(row_ptr, b->d_seg_first, b->d_seg_last, b->d_nnz, n, s);
     if (e != hipSuccess) return hip_fail(e, "nnz launch");
@@ -1025,8 +1038,7 @@ static int fill_impl(const ci_basis* b, const float* tbme, const int64_t* row_pt
     if (!b || !row_ptr) return fail(CI_EINVAL, "null pointer");
     if (int rc = need_ready(b)) return rc;
     if (!tbme && b->n_tbme > 0) return fail(CI_EINVAL, "null pointer");
-    hipError_t e = launch_fill(b->d_bases, (int)b->info.size(), b->d_basis_row0, b->nrows, tbme, row_ptr,
-                               b->n_rowptr, col, val, keys, b->tune, b->d_queue, full, s);
+    hipError_t e = launch_fill(b->d_bases, b->rows, tbme, row_ptr, b->n_rowptr, col, val, keys, b->tune, b->d_queue, full, s);
     if (e != hipSuccess) return hip_fail(e, "fill launch");
     return CI_OK;
 }
@@ -1459,8 +1471,7 @@ int ci_hamiltonian_tune(ci_basis* b, const float* tbme, const int64_t* row_ptr, 
             b->tune.row_grab = grab < 0 ? 0 : grab;
             b->tune.row_xcd = grab < 0 ? 1 : 0;
             float ms = 0.0f;
-            rc = time_ms([&] { return launch_fill(b->d_bases, (int)b->info.size(), b->d_basis_row0, b->nrows, tbme,
-                                                  row_ptr, b->n_rowptr, col, val, nullptr, b->tune, b->d_queue, 0,
+            rc = time_ms([&] { return launch_fill(b->d_bases, b->rows, tbme, row_ptr, b->n_rowptr, col, val, nullptr, b->tune, b->d_queue, 0,
                                                   s); },
                          reps, s, e0, e1, &ms);
             if (rc == CI_OK && (!have || ms < best_ms)) {
@@ -1500,7 +1511,7 @@ int ci_hamiltonian_tune(ci_basis* b, const float* tbme, const int64_t* row_ptr, 
     // fill writes the words once, then its own tiles x (grid, persistent)
     if (keys && rc == CI_OK) {
         b->tune = best;
-        e = launch_fill(b->d_bases, (int)b->info.size(), b->d_basis_row0, b->nrows, tbme, row_ptr, b->n_rowptr, col,
+        e = launch_fill(b->d_bases, b->rows, tbme, row_ptr, b->n_rowptr, col,
                         val, keys, b->tune, b->d_queue, 0, s);
         if (e != hipSuccess) rc = hip_fail(e, "autotune fill with stored words");
         have = false;
@@ -1532,7 +1543,7 @@ int ci_hamiltonian_tune(ci_basis* b, const float* tbme, const int64_t* row_ptr, 
     b->tune = best;
     remember_tuning(b->probs, best);
     // leave col / val (/ keys) / grad_tbme as the chosen shapes compute them
-    e = launch_fill(b->d_bases, (int)b->info.size(), b->d_basis_row0, b->nrows, tbme, row_ptr, b->n_rowptr, col,
+    e = launch_fill(b->d_bases, b->rows, tbme, row_ptr, b->n_rowptr, col,
                     val, keys, b->tune, b->d_queue, 0, s);
     if (e == hipSuccess) e = vjp_launch(b, row_ptr, grad_val, grad_tbme, work, b->tune, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -58,6 +58,8 @@ struct SpeciesDev {
     const uint64_t* l12;     // d<=2 partners in keys of the same 2M and Nq parity
     const int32_t* seg1;     // [nsd][nk + 1] first record of each key in l1(x)
     const int32_t* seg12;    // [nsd][nk + 1] same for l12(x)
+    const int32_t* segT1;    // [nk + 1][nsd] seg1 transposed
+    const int32_t* segT12;   // [nk + 1][nsd] seg12 transposed
     const int32_t* self12;   // [nsd] position of x itself inside its own key segment of l12(x)
     int32_t nsd, nk;
 };
@@ -87,6 +89,19 @@ struct BasisDev {
     double hw;
 };
 
+// How the row passes take the rows of a handle, per block of the global block
+// list (every block of every basis of the batch): the fill takes one row per
+// wavefront; the count takes groups of up to kGroupRows rows of one proton
+// determinant.
+constexpr int kGroupRows = 16;
+struct RowWork {
+    const int32_t* blk_basis;  // [nblocks] basis of the block
+    const int32_t* blk_local;  // [nblocks] its block in that basis
+    const int64_t* row_off;    // [nblocks + 1] rows of the blocks before
+    const int64_t* group_off;  // [nblocks + 1] groups of the blocks before
+    int nblocks;
+    int64_t nrows, ngroups;    // the last elements of the two offsets
+};
 
 // Adjoint: the table positions of one basis are cut into buckets of 2^bits
 // consecutive positions (bits >= kAdjBucketMinBits, chosen so that a basis has
@@ -163,6 +178,8 @@ struct PartnerArgs {
     uint64_t* l12;
     int32_t* seg1;  // [nsd][nk + 1]
     int32_t* seg12;
+    int32_t* segT1;  // [nk + 1][nsd]
+    int32_t* segT12;
     int32_t* self12;
     int32_t nsd, nk, W;
 };

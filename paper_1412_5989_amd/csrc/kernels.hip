@@ -24,8 +24,9 @@
 // per two-body term, a segmented wave reduction in a fixed order), so a long
 // sum never stalls the other 63 lanes.
 //
-// The same walk serves the count pass (steps 1-2 only), the fill pass and the
-// adjoint (step 3 scatters phase * upstream value onto the table).
+// The same walk serves the fill pass and the adjoint (step 3 scatters phase *
+// upstream value onto the table).  The count pass needs no walk: the number of
+// entries follows from the sizes of the partner segments (count_kernel).
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -34,7 +35,7 @@
 
 namespace ci {
 
-enum { kCount = 0, kFill = 1, kAdjoint = 2 };
+enum { kFill = 1, kAdjoint = 2 };
 
 constexpr int kWavesPerBlock = 4;
 constexpr int kQueue = 96;  // queued multi-term entries per wave
@@ -721,9 +722,9 @@ __device__ void row_occ(const BasisDev& B, WaveLds& L, RowView& R, int gP, int g
     R.spe_sum = ((double)shells + 1.5 * A) * B.hw * (B.kinetic ? 0.5 : 1.0);
 }
 
-// One row: count (returns the number of entries), fill or adjoint.
+// One row: fill or adjoint.
 template <int MODE>
-__device__ int64_t do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView& R)
+__device__ void do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView& R)
 {
     const int lane = threadIdx.x & 63;
     const SpeciesDev& SP = B.sp[0];
@@ -745,7 +746,7 @@ __device__ int64_t do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView&
     const gptr<int32_t> sN12 = glb(SN.seg12 + (int64_t)gN * (nkn + 1));
     const int self12 = uniform(cst(SN.self12)[gN]);
 
-    if (MODE != kCount) row_occ(B, L, R, gP, gN, MODE == kFill);
+    row_occ(B, L, R, gP, gN, MODE == kFill);
 
     int64_t pos = 0;  // entries of the row so far
     int qn = 0;       // queued multi-term entries
@@ -755,7 +756,6 @@ __device__ int64_t do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView&
         //    the row's neutron partners, column base
         const int b2 = w0 + lane;
         int np = 0, bp = 0, bcol = 0, bstr = 0, bn1 = 0, bl1 = 0, bn12 = 0, bl12 = 0;
-        int64_t blen = 0;  // count pass: entries of the lane's block (other blocks than the row's)
         if (b2 < B.nblk) {
             const i32x4 bk = glb((const i32x4*)B.blk)[b2];  // one 16-byte load
             const int kp2 = bk.x, kn2 = bk.y;
@@ -773,23 +773,6 @@ __device__ int64_t do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView&
             // (d <= 1 for a moved proton, d <= 2 for P' = P): otherwise every
             // segment of the block is empty
             if (!same_n && bl1 == 0 && (kp2 != kp || bl12 == 0)) np = 0;
-            if (MODE == kCount && (b2 != bi || R.full)) {
-                // entries of a block other than the row's own, from the per-key
-                // counts: P' = P gives bl12, every one-proton move bl1, every
-                // two-proton move (same neutron key only) one entry
-                const int d0 = kp2 == kp ? 1 : 0;
-                const int c1 = sP1[kp2 + 1] - sP1[kp2];  // d <= 1 partners of P in Kp'
-                const int c12 = same_n ? np : c1;         // d <= 2 partners (same 2M and parity keys)
-                blen = (int64_t)(c12 - c1) + (int64_t)(c1 - d0) * bl1 + (int64_t)d0 * bl12;
-                np = 0;
-            }
-        }
-        if (MODE == kCount) {
-            // only the row's own block (lane 0 of the first window) is walked
-            // segment by segment: it is cut at the diagonal
-            int64_t t = blen;
-            for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-            pos += t;
         }
         const int bincl = wave_incl_scan(np);
         const int bstart = bincl - np;  // first segment of the lane's block
@@ -826,10 +809,6 @@ __device__ int64_t do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView&
             }
             const int eincl = wave_incl_scan(len);
             const int T = lane63(eincl);
-            if (MODE == kCount) {
-                pos += T;
-                continue;
-            }
             const int estart = eincl - len;  // first entry of the lane's segment
             // 3. the entries of the chunk, 64 consecutive ones per round
             clear_marks(L);
@@ -888,13 +867,11 @@ __device__ int64_t do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView&
                         st32(R.keys + base, ue, special ? (kKeySpecial | qr)
                                                         : (key >= 0 ? ((uint32_t)key | (neg ? kKeyNeg : 0u)) : kKeyNone));
                 }
-                if (MODE != kCount) {
-                    // the diagonal entry (nothing moved) is treated on its own
-                    const bool diag = special && q_kind(qr) == 0;
-                    const uint64_t md = __ballot(diag);
-                    if (md) diag_at = __builtin_amdgcn_readlane((int)(pos + e), __ffsll((long long)md) - 1);
-                    special = special && !diag;
-                }
+                // the diagonal entry (nothing moved) is treated on its own
+                const bool diag = special && q_kind(qr) == 0;
+                const uint64_t md = __ballot(diag);
+                if (md) diag_at = __builtin_amdgcn_readlane((int)(pos + e), __ffsll((long long)md) - 1);
+                special = special && !diag;
                 const uint64_t m = __ballot(special);
                 if (m) {
                     const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -914,9 +891,8 @@ __device__ int64_t do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView&
             pos += T;
         }
     }
-    if (MODE != kCount) flush_queue<MODE, true>(R, L, qn);
-    if (MODE != kCount && diag_at >= 0) row_diagonal<MODE>(R, L, R.pos0 + diag_at);
-    return pos;
+    flush_queue<MODE, true>(R, L, qn);
+    if (diag_at >= 0) row_diagonal<MODE>(R, L, R.pos0 + diag_at);
 }
 
 // Adjoint of one row from the words the fill stored (R.keys): the row's
@@ -969,48 +945,23 @@ __device__ void do_row_keys(const BasisDev& B, WaveLds& L, int bi, int r, RowVie
     flush_queue<kAdjoint, false>(R, L, qn);
 }
 
-template <int MODE>
-__device__ __forceinline__ void run_row_at(const BasisDev& B, int bi, int i, int r, const float* __restrict__ tbme,
-                                           int64_t* __restrict__ row_ptr, int64_t nrp, int32_t* __restrict__ col,
-                                           float* __restrict__ val, const float* __restrict__ gval,
-                                           unsigned long long* __restrict__ gacc, lptr<uint32_t> hkey,
-                                           lptr<int32_t> hval, bool use_table, int hbits, int qshift, bool full,
-                                           uint32_t* keys, WaveLds& L);
-
-// Row grow of the batch (rows of all bases are numbered consecutively) on the
-// calling wavefront.
-template <int MODE>
-__device__ __forceinline__ void run_row(const BasisDev* __restrict__ bases, int nb,
-                                        const int64_t* __restrict__ basis_row0, int64_t grow,
-                                        const float* __restrict__ tbme, int64_t* __restrict__ row_ptr,
-                                        int64_t nrp, int32_t* __restrict__ col, float* __restrict__ val,
-                                        const float* __restrict__ gval, unsigned long long* __restrict__ gacc,
-                                        lptr<uint32_t> hkey, lptr<int32_t> hval, bool use_table, bool full,
-                                        uint32_t* keys, WaveLds& L)
+// Block of item u of a list of items per block (global block list): the
+// largest gb with off[gb] <= u (every block that owns an item has off[gb] < off[gb + 1]).
+__device__ __forceinline__ int block_of(const int64_t* off, int nblocks, int64_t u)
 {
-    // basis of the row (few bases: linear search)
-    int b = 0;
-    while (b + 1 < nb && cst(basis_row0)[b + 1] <= grow) b++;
-    b = uniform(b);
-    const BasisDev& B = bases[b];
-    const int i = uniform((int)(grow - cst(basis_row0)[b]));
-    // block of the row
-    const cptr<int64_t> blk_off = cst(B.blk_off);
-    int lo = 0, hi = B.nblk;
+    int lo = 0, hi = nblocks;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (blk_off[mid] <= i) lo = mid;
+        if (cst(off)[mid] <= u) lo = mid;
         else hi = mid;
     }
-    const int bi = uniform(lo);
-    run_row_at<MODE>(B, bi, i, i - (int)blk_off[bi], tbme, row_ptr, nrp, col, val, gval, gacc, hkey, hval, use_table,
-                     0, 0, full, keys, L);
+    return uniform(lo);
 }
 
 // Row i of basis B, row r of its block bi.
 template <int MODE>
 __device__ __forceinline__ void run_row_at(const BasisDev& B, int bi, int i, int r, const float* __restrict__ tbme,
-                                           int64_t* __restrict__ row_ptr, int64_t nrp, int32_t* __restrict__ col,
+                                           const int64_t* __restrict__ row_ptr, int64_t nrp, int32_t* __restrict__ col,
                                            float* __restrict__ val, const float* __restrict__ gval,
                                            unsigned long long* __restrict__ gacc, lptr<uint32_t> hkey,
                                            lptr<int32_t> hval, bool use_table, int hbits, int qshift, bool full,
@@ -1034,42 +985,52 @@ __device__ __forceinline__ void run_row_at(const BasisDev& B, int bi, int i, int
     R.NN = B.NN;
     R.spe_sum = 0.0;
     R.full = full;
-    if (MODE == kCount) {
-        R.pos0 = 0;
-        R.cap = 0;
-        const int64_t n = do_row<kCount>(B, L, bi, r, R);
-        if ((threadIdx.x & 63) == 0) glbw(row_ptr)[B.row0 + i + 1] = n;
-    } else {
-        R.pos0 = uniform64(cst(row_ptr)[B.row0 + i]);
-        R.cap = uniform64(cst(row_ptr)[nrp - 1]);  // the entries of all bases end here
-        if (MODE == kAdjoint && keys)
-            do_row_keys(B, L, bi, r, R, uniform64(cst(row_ptr)[B.row0 + i + 1]));
-        else
-            do_row<MODE>(B, L, bi, r, R);
-    }
+    R.pos0 = uniform64(cst(row_ptr)[B.row0 + i]);
+    R.cap = uniform64(cst(row_ptr)[nrp - 1]);  // the entries of all bases end here
+    if (MODE == kAdjoint && keys)
+        do_row_keys(B, L, bi, r, R, uniform64(cst(row_ptr)[B.row0 + i + 1]));
+    else
+        do_row<MODE>(B, L, bi, r, R);
 }
 
-// Count and fill.  grab == 0: one wavefront per row over a grid of all rows.
+// Row g of the batch (row_off[gb]: rows of the blocks before gb of the global
+// block list) on the calling wavefront, fill.
+__device__ __forceinline__ void fill_row(const BasisDev* __restrict__ bases, const int32_t* __restrict__ blk_basis,
+                                         const int32_t* __restrict__ blk_local, int nblocks,
+                                         const int64_t* __restrict__ row_off, int64_t g, const float* __restrict__ tbme,
+                                         const int64_t* __restrict__ row_ptr, int64_t nrp, int32_t* __restrict__ col,
+                                         float* __restrict__ val, bool full, uint32_t* keys, WaveLds& L)
+{
+    const int gb = block_of(row_off, nblocks, g);
+    const BasisDev& B = bases[uniform(cst(blk_basis)[gb])];
+    const int bi = uniform(cst(blk_local)[gb]), r = uniform((int)(g - cst(row_off)[gb]));
+    run_row_at<kFill>(B, bi, uniform((int)cst(B.blk_off)[bi]) + r, r, tbme, row_ptr, nrp, col, val, nullptr, nullptr,
+                      nullptr, nullptr, false, 0, 0, full, keys, L);
+}
+
+// Fill.  grab == 0: one wavefront per row over a grid of all rows.
 // grab > 0: a persistent grid; each wavefront takes grab consecutive rows at a
 // time from the work counter *queue (zero at launch) until none are left.
 // Eight wavefronts per SIMD (the compiler keeps the fill within 64 VGPRs and
 // spills a few registers): the fill is issue bound and the extra wavefront
 // hides more of its load latency (10B fill 1.61 -> 1.54 ms, 6Li 0.64 -> 0.59).
-template <int MODE, int WAVES>
+template <int WAVES>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(8, 8)))
-    row_kernel(const BasisDev* __restrict__ bases, int nb, const int64_t* __restrict__ basis_row0,
-               int64_t nrows, const float* __restrict__ tbme, int64_t* __restrict__ row_ptr, int64_t nrp,
+    row_kernel(const BasisDev* __restrict__ bases, const int32_t* __restrict__ blk_basis,
+               const int32_t* __restrict__ blk_local, int nblocks, const int64_t* __restrict__ row_off,
+               const float* __restrict__ tbme, const int64_t* __restrict__ row_ptr, int64_t nrp,
                int32_t* __restrict__ col, float* __restrict__ val, uint32_t* __restrict__ keys, int grab,
                unsigned long long* __restrict__ queue, int full, int xcd)
 {
     __shared__ WaveLds lds[WAVES];
     const int wid = uniform(threadIdx.x >> 6);
+    const int64_t nrows = uniform64(cst(row_off)[nblocks]);
     if (grab <= 0) {
         const int64_t wg = xcd ? xcd_contiguous(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
-        const int64_t grow = wg * WAVES + wid;
-        if (grow < nrows)
-            run_row<MODE>(bases, nb, basis_row0, grow, tbme, row_ptr, nrp, col, val, nullptr, nullptr, nullptr,
-                          nullptr, false, full != 0, keys, lds[wid]);
+        const int64_t g = wg * WAVES + wid;
+        if (g < nrows)
+            fill_row(bases, blk_basis, blk_local, nblocks, row_off, g, tbme, row_ptr, nrp, col, val, full != 0, keys,
+                     lds[wid]);
         return;
     }
     for (;;) {
@@ -1081,9 +1042,127 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
         if (g0 >= nrows) break;
         const int64_t g1 = g0 + grab < nrows ? g0 + grab : nrows;
         for (int64_t g = g0; g < g1; g++)
-            run_row<MODE>(bases, nb, basis_row0, g, tbme, row_ptr, nrp, col, val, nullptr, nullptr, nullptr,
-                          nullptr, false, full != 0, keys, lds[wid]);
+            fill_row(bases, blk_basis, blk_local, nblocks, row_off, g, tbme, row_ptr, nrp, col, val, full != 0, keys,
+                     lds[wid]);
     }
+}
+
+// ------------------------------------------------------------------ count
+//
+// Entries per row.  Rows (P, N) that share their proton determinant P form
+// groups of up to kGroupRows consecutive N; one wavefront takes a group.  In a
+// target block (Kp', Kn') row (P, N) stores T1 l1(N) + T2 + T0 l12(N) entries,
+// with T1, T2, T0 the partners of P in Kp' that move one, two (same Kn only)
+// and no protons and l1, l12 the d <= 1 and d <= 2 partners of N in Kn', so only
+// the segment tables are read: those of P once per group, those of N by
+// neighbouring lanes for neighbouring N (seg*T).  One row per wavefront, with
+// the tables of each row read on their own, the pass took 334 us on 10B Nmax = 4
+// and 145 us on 6Li Nmax = 6, scan and read-back included; with groups of 16 it
+// takes 89 and 61 us (groups of 8: 108 and 67, of 4: 161 and 87).
+
+// One group of block bi: P, its rows and their place in row_ptr.
+struct GroupView {
+    int kp, kn, nr, gP, gN0, selfP;
+    int64_t row;  // row_ptr index of the first row
+};
+__device__ __forceinline__ GroupView group_view(const BasisDev& B, int bi, int u)
+{
+    const SpeciesDev& SP = B.sp[0];
+    const SpeciesDev& SN = B.sp[1];
+    GroupView G;
+    G.kp = uniform(cst(B.blk_kp)[bi]);
+    G.kn = uniform(cst(B.blk_kn)[bi]);
+    const int nKn = uniform(cst(SN.key_off)[G.kn + 1] - cst(SN.key_off)[G.kn]);
+    const int ng = (nKn + kGroupRows - 1) / kGroupRows, R = (nKn + ng - 1) / ng;
+    const int ip = u / ng, in0 = (u - ip * ng) * R;
+    G.nr = min(R, nKn - in0);
+    G.gP = uniform(cst(SP.key_off)[G.kp] + ip);
+    G.gN0 = uniform(cst(SN.key_off)[G.kn] + in0);
+    G.selfP = uniform(cst(SP.self12)[G.gP]);
+    G.row = B.row0 + uniform64(cst(B.blk_off)[bi]) + (int64_t)ip * nKn + in0;
+    return G;
+}
+
+// The lane's target block w0 + lane: its neutron key and the partners of P in
+// Kp' that move no (t0), one (t1) and two (t2) protons; in the group's own
+// block of the upper triangle (lane 0 when w0 == bi) those from P on.  Every lane of the
+// wavefront calls it.
+struct GroupBlock {
+    int kn, t0, t1, t2;
+};
+__device__ __forceinline__ GroupBlock group_block(const BasisDev& B, const GroupView& G, int bi, int w0, bool full)
+{
+    const int lane = threadIdx.x & 63, b2 = w0 + lane;
+    const SpeciesDev& SP = B.sp[0];
+    const gptr<int32_t> s1 = glb(SP.seg1 + (int64_t)G.gP * (SP.nk + 1)), s12 = glb(SP.seg12 + (int64_t)G.gP * (SP.nk + 1));
+    GroupBlock q{0, 0, 0, 0};
+    if (b2 < B.nblk) {
+        const i32x4 bk = glb((const i32x4*)B.blk)[b2];
+        const int c1 = s1[bk.x + 1] - s1[bk.x];
+        q.kn = bk.y;
+        q.t0 = bk.x == G.kp ? 1 : 0;
+        q.t1 = c1 - q.t0;
+        if (bk.y == G.kn) q.t2 = s12[bk.x + 1] - s12[bk.x] - c1;
+    }
+    if (w0 == bi && !full) {
+        const gptr<uint64_t> P12 = glb(SP.l12 + uniform64(cst(SP.l12_ptr)[G.gP]));
+        const int p0 = uniform(s12[G.kp]) + G.selfP, p1 = uniform(s12[G.kp + 1]);
+        int c1 = 0, c2 = 0;
+        for (int p = p0; p < p1; p += 64) {
+            const int d = p + lane < p1 ? rec_d(P12[p + lane]) : 3;
+            c1 += __popcll(__ballot(d == 1));
+            c2 += __popcll(__ballot(d == 2));
+        }
+        if (lane == 0) {
+            q.t1 = c1;
+            q.t2 = c2;
+        }
+    }
+    return q;
+}
+
+// group_off[gb] (global block list) is the number of groups of the blocks
+// before gb; ngroups their total.
+__global__ void __launch_bounds__(256)
+    count_kernel(const BasisDev* __restrict__ bases, const int32_t* __restrict__ blk_basis,
+                 const int32_t* __restrict__ blk_local, int nblocks, const int64_t* __restrict__ group_off,
+                 int64_t ngroups, int64_t* __restrict__ row_ptr, int full)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t u = (int64_t)blockIdx.x * 4 + uniform(threadIdx.x >> 6);
+    if (u >= ngroups) return;
+    const int gb = block_of(group_off, nblocks, u);
+    const BasisDev& B = bases[uniform(cst(blk_basis)[gb])];
+    const int bi = uniform(cst(blk_local)[gb]);
+    const GroupView G = group_view(B, bi, uniform((int)(u - cst(group_off)[gb])));
+    // lanes take (row, block) pairs, 64 / kGroupRows blocks per step
+    constexpr int kBlocks = 64 / kGroupRows;
+    const SpeciesDev& SN = B.sp[1];
+    const int r = lane % kGroupRows;
+    const int64_t n = SN.nsd, gN = G.gN0 + (r < G.nr ? r : 0);
+    const int selfN = glb(SN.self12)[gN];
+    int64_t tot = 0;
+    for (int w0 = full ? 0 : bi; w0 < B.nblk; w0 += 64) {
+        const GroupBlock q = group_block(B, G, bi, w0, full != 0);
+        for (uint64_t cand = __ballot(q.t0 + q.t1 + q.t2 > 0); cand;) {
+            int t = 64;  // the lane's block of this step, 64: none
+#pragma unroll
+            for (int k = 0; k < kBlocks; k++) {
+                const int tt = cand ? __ffsll((long long)cand) - 1 : 64;
+                cand &= cand - 1;
+                if (lane / kGroupRows == k) t = tt;
+            }
+            const int kn2 = lane_read(q.kn, t & 63), t0 = lane_read(q.t0, t & 63), t1 = lane_read(q.t1, t & 63),
+                      t2 = lane_read(q.t2, t & 63);
+            if (t < 64) {
+                const gptr<int32_t> s1 = glb(SN.segT1 + (int64_t)kn2 * n + gN), s12 = glb(SN.segT12 + (int64_t)kn2 * n + gN);
+                tot += (int64_t)t1 * (s1[n] - s1[0]) + t2;
+                if (t0) tot += s12[n] - s12[0] - (w0 + t == bi && !full ? selfN : 0);
+            }
+        }
+    }
+    for (int o = kGroupRows; o < 64; o <<= 1) tot += __shfl_xor(tot, o, 64);
+    if (lane < G.nr) glbw(row_ptr)[G.row + lane + 1] = tot;
 }
 
 // Adjoint row groups: each block (proton key Kp, neutron key Kn) is cut into
@@ -1248,7 +1327,7 @@ __global__ void __launch_bounds__(64 * WAVES)
             if (t >= cnt) break;
             const int u = t / tn, v = t - u * tn;
             const int r = (ip0 + u) * nKn + in0 + v;
-            run_row_at<kAdjoint>(B, bi, uniform((int)cst(B.blk_off)[bi] + r), r, nullptr, const_cast<int64_t*>(row_ptr), nrp,
+            run_row_at<kAdjoint>(B, bi, uniform((int)cst(B.blk_off)[bi] + r), r, nullptr, row_ptr, nrp,
                                  nullptr, nullptr, gval, gacc, (lptr<uint32_t>)hkey, (lptr<int32_t>)hval,
                                  use_table != 0, SLOT_BITS, qshift, false, const_cast<uint32_t*>(keys), lds[wid]);
         }
@@ -1651,45 +1730,12 @@ static unsigned resident_blocks(const void* kernel, int threads, int kind)
     return (unsigned)v;
 }
 
-template <int MODE, int WAVES>
-static void launch_rows_w(const BasisDev* bases, int nb, const int64_t* basis_row0, int64_t nrows,
-                          const float* tbme, int64_t* row_ptr, int64_t nrp, int32_t* col, float* val, uint32_t* keys,
-                          int grab, unsigned long long* queue, int full, int xcd, hipStream_t s)
+hipError_t launch_count(const BasisDev* bases, int nb, const RowWork& w, int64_t* row_ptr, int64_t nrp,
+                        const int64_t* seg_first, int64_t* scan_tmp, int full, hipStream_t s)
 {
-    unsigned grid = grid_for(nrows, WAVES);
-    if (grab > 0) {
-        hipLaunchKernelGGL(zero_u64, dim3(1), dim3(1), 0, s, queue);
-        const unsigned res = resident_blocks((const void*)row_kernel<MODE, WAVES>, 64 * WAVES,
-                                             2 * MODE + (WAVES == 8 ? 1 : 0));
-        const unsigned need = grid_for(nrows, WAVES * grab);
-        grid = res < need ? res : need;
-    }
-    hipLaunchKernelGGL((row_kernel<MODE, WAVES>), dim3(grid), dim3(64 * WAVES), 0, s, bases, nb, basis_row0,
-                       nrows, tbme, row_ptr, nrp, col, val, keys, grab, queue, full, xcd);
-}
-
-template <int MODE>
-static hipError_t launch_rows(const BasisDev* bases, int nb, const int64_t* basis_row0, int64_t nrows,
-                              const float* tbme, int64_t* row_ptr, int64_t nrp, int32_t* col, float* val,
-                              uint32_t* keys, const ci_tuning& t, unsigned long long* queue, int full, hipStream_t s)
-{
-    if (nrows <= 0) return hipSuccess;
-    if (t.row_waves == 8)
-        launch_rows_w<MODE, 8>(bases, nb, basis_row0, nrows, tbme, row_ptr, nrp, col, val, keys, t.row_grab, queue,
-                               full, t.row_xcd, s);
-    else
-        launch_rows_w<MODE, 4>(bases, nb, basis_row0, nrows, tbme, row_ptr, nrp, col, val, keys, t.row_grab, queue,
-                               full, t.row_xcd, s);
-    return hipGetLastError();
-}
-
-hipError_t launch_count(const BasisDev* bases, int nb, const int64_t* basis_row0, int64_t nrows,
-                        int64_t* row_ptr, int64_t nrp, const int64_t* seg_first, int64_t* scan_tmp,
-                        const ci_tuning& t, unsigned long long* queue, int full, hipStream_t s)
-{
-    hipError_t e = launch_rows<kCount>(bases, nb, basis_row0, nrows, nullptr, row_ptr, nrp, nullptr, nullptr,
-                                       nullptr, t, queue, full, s);
-    if (e != hipSuccess) return e;
+    if (w.ngroups > 0)
+        hipLaunchKernelGGL(count_kernel, dim3(grid_for(w.ngroups, 4)), dim3(256), 0, s, bases, w.blk_basis,
+                           w.blk_local, w.nblocks, w.group_off, w.ngroups, row_ptr, full);
     // the first slot of each basis' segment holds 0 before the scan, so the
     // inclusive scan leaves there the number of entries of the bases before it
     hipLaunchKernelGGL(zero_i64_at, dim3(grid_for(nb, 256)), dim3(256), 0, s, row_ptr, seg_first, nb);
@@ -1703,12 +1749,32 @@ hipError_t launch_nnz(const int64_t* row_ptr, const int64_t* first, const int64_
     return hipGetLastError();
 }
 
-hipError_t launch_fill(const BasisDev* bases, int nb, const int64_t* basis_row0, int64_t nrows,
-                       const float* tbme, const int64_t* row_ptr, int64_t nrp, int32_t* col, float* val,
-                       uint32_t* keys, const ci_tuning& t, unsigned long long* queue, int full, hipStream_t s)
+template <int WAVES>
+static void launch_fill_w(const BasisDev* bases, const RowWork& w, const float* tbme, const int64_t* row_ptr,
+                          int64_t nrp, int32_t* col, float* val, uint32_t* keys, int grab, unsigned long long* queue,
+                          int full, int xcd, hipStream_t s)
 {
-    return launch_rows<kFill>(bases, nb, basis_row0, nrows, tbme, const_cast<int64_t*>(row_ptr), nrp, col, val, keys,
-                              t, queue, full, s);
+    unsigned grid = grid_for(w.nrows, WAVES);
+    if (grab > 0) {
+        hipLaunchKernelGGL(zero_u64, dim3(1), dim3(1), 0, s, queue);
+        const unsigned res = resident_blocks((const void*)row_kernel<WAVES>, 64 * WAVES, WAVES == 8 ? 3 : 2);
+        const unsigned need = grid_for(w.nrows, WAVES * grab);
+        grid = res < need ? res : need;
+    }
+    hipLaunchKernelGGL((row_kernel<WAVES>), dim3(grid), dim3(64 * WAVES), 0, s, bases, w.blk_basis, w.blk_local,
+                       w.nblocks, w.row_off, tbme, row_ptr, nrp, col, val, keys, grab, queue, full, xcd);
+}
+
+hipError_t launch_fill(const BasisDev* bases, const RowWork& w, const float* tbme, const int64_t* row_ptr, int64_t nrp,
+                       int32_t* col, float* val, uint32_t* keys, const ci_tuning& t, unsigned long long* queue, int full,
+                       hipStream_t s)
+{
+    if (w.nrows <= 0) return hipSuccess;
+    if (t.row_waves == 8)
+        launch_fill_w<8>(bases, w, tbme, row_ptr, nrp, col, val, keys, t.row_grab, queue, full, t.row_xcd, s);
+    else
+        launch_fill_w<4>(bases, w, tbme, row_ptr, nrp, col, val, keys, t.row_grab, queue, full, t.row_xcd, s);
+    return hipGetLastError();
 }
 
 hipError_t launch_vjp(const BasisDev* bases, int nbases, const int32_t* blk_basis, const int32_t* blk_local,
