@@ -351,13 +351,27 @@ std::vector<std::tuple<int, int, int, int, int, double, int>> tune_key(const std
     return k;
 }
 
-ci_tuning default_tuning() { return ci_tuning{4, 0, 64, 8, 1, 96, 8, 1, 0, 0, 0}; }
+// Launch shapes of a handle that was not tuned.  The adjoint: 16 wavefronts on
+// a 16384-slot table, its slots added to the accumulators by atomics.  The
+// atomics overlap the walk of other tiles, while tile records (the other
+// flush) cost a reduction of 0.1-0.6 ms after it; the wide table merges more
+// of them per tile.  Measured (us per adjoint, 64 x 8 rows on the narrow
+// table with records -> the shape below): D = 59 59 -> 33, 952 147 -> 42,
+// 15,764 440 -> 108, 48,917 540 -> 259, 186,894 2040 -> 1143, 288,930 1497 ->
+// 1269, 581,740 2709 -> 2650.  Small bases give too few tiles of 64 rows to
+// fill the 256 CUs, so they are cut finer: at 15,764 rows 64-row tiles take
+// 132 us and 32-row tiles 108, at 48,917 rows 259 and 257.
+ci_tuning default_tuning(int64_t nrows)
+{
+    const int adj_rows = nrows < 32768 ? 32 : 64;
+    return ci_tuning{4, 0, adj_rows, 16, 1, 96, 8, 1, 0, 1, 1};
+}
 
-ci_tuning cached_tuning(const std::vector<ci_problem>& p)
+ci_tuning cached_tuning(const std::vector<ci_problem>& p, int64_t nrows)
 {
     std::lock_guard<std::mutex> g(g_tune_mu);
     auto it = g_tune.find(tune_key(p));
-    return it == g_tune.end() ? default_tuning() : it->second;
+    return it == g_tune.end() ? default_tuning(nrows) : it->second;
 }
 
 void remember_tuning(const std::vector<ci_problem>& p, const ci_tuning& t)
@@ -896,7 +910,7 @@ int ci_basis_build(const ci_problem* probs, int32_t n_probs, ci_basis_info* info
     h->d_adjb = (AdjBasis*)D(P->o_adjb);
     h->nblocks = P->nblocks;
     h->probs.assign(probs, probs + n_probs);
-    h->tune = cached_tuning(h->probs);
+    h->tune = cached_tuning(h->probs, h->nrows);
     h->n_rowptr = R;
     h->n_tbme = T;
     // the partner lists are still being counted on the stream
