@@ -226,7 +226,7 @@ void fill_info(const HostBasis& hb, ci_basis_info& in)
 
 // offsets of one species' tables in the arena
 struct SpOff {
-    size_t sd, sdT, sd_key, key_off, key_nq, key_m2, l1_ptr, l12_ptr, seg1, seg12, segT1, segT12, self12;
+    size_t sd, sd_key, key_off, key_nq, key_m2, kmap, l1_ptr, l12_ptr, seg1, seg12, segT1, segT12, self12;
 };
 struct UOff {
     SpOff sp[2];
@@ -518,11 +518,11 @@ int plan_build(const ci_problem* probs, int32_t n_probs, BuildPlan& P, std::stri
             const size_t nsd = (size_t)sp.nsd(), nk = (size_t)sp.nk();
             const size_t s0 = L.off;
             o.sd = L.take<uint64_t>(sp.sd.size());
-            o.sdT = L.take<uint64_t>(sp.sd.size());
             o.sd_key = L.take<int32_t>(nsd);
             o.key_off = L.take<int32_t>(nk + 1);
             o.key_nq = L.take<int32_t>(nk);
             o.key_m2 = L.take<int32_t>(nk);
+            o.kmap = L.take<int32_t>(sp.kmap.size());
             ubytes[u] += L.off - s0;
         }
         const size_t s0 = L.off;
@@ -598,7 +598,6 @@ PartnerArgs partner_args(const ci_basis& h, size_t u, int sidx)
     char* dev = h.arena;
     PartnerArgs a{};
     a.sd = (const uint64_t*)(dev + o.sd);
-    a.sdT = (const uint64_t*)(dev + o.sdT);
     a.sd_key = (const int32_t*)(dev + o.sd_key);
     a.key_off = (const int32_t*)(dev + o.key_off);
     a.key_nq = (const int32_t*)(dev + o.key_nq);
@@ -610,6 +609,14 @@ PartnerArgs partner_args(const ci_basis& h, size_t u, int sidx)
     a.segT1 = (int32_t*)(dev + o.segT1);
     a.segT12 = (int32_t*)(dev + o.segT12);
     a.self12 = (int32_t*)(dev + o.self12);
+    a.orb_qn = (const int32_t*)(dev + h.uo[u].orb_qn);
+    a.kmap = (const int32_t*)(dev + o.kmap);
+    a.nsps = h.uniq[u]->nsps;
+    a.budget = sp.budget;
+    a.kmap_nq0 = sp.kmap_nq0;
+    a.kmap_m20 = sp.kmap_m20;
+    a.kmap_nq = sp.kmap_nq;
+    a.kmap_m2 = sp.kmap_m2;
     a.nsd = (int32_t)sp.nsd();
     a.nk = sp.nk();
     a.W = h.uniq[u]->W;
@@ -730,16 +737,11 @@ int ci_basis_build(const ci_problem* probs, int32_t n_probs, ci_basis_info* info
             const HostSpecies& sp = hb.sp[sidx];
             const SpOff& o = P->uo[u].sp[sidx];
             put(o.sd, sp.sd.data(), sp.sd.size() * 8);
-            {
-                const int64_t nsd = sp.nsd();
-                uint64_t* Tw = (uint64_t*)(mirror + o.sdT);
-                for (int64_t x = 0; x < nsd; x++)
-                    for (int w = 0; w < hb.W; w++) Tw[(int64_t)w * nsd + x] = sp.sd[x * hb.W + w];
-            }
             put(o.sd_key, sp.sd_key.data(), sp.sd_key.size() * 4);
             put(o.key_off, sp.key_off.data(), sp.key_off.size() * 4);
             put(o.key_nq, sp.key_nq.data(), sp.key_nq.size() * 4);
             put(o.key_m2, sp.key_m2.data(), sp.key_m2.size() * 4);
+            put(o.kmap, sp.kmap.data(), sp.kmap.size() * 4);
         }
         const UOff& U = P->uo[u];
         put(U.blk_kp, hb.blk_kp.data(), hb.blk_kp.size() * 4);

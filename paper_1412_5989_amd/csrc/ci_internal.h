@@ -143,6 +143,10 @@ struct HostSpecies {
     int budget = 0;                 // largest Nq of one determinant
     std::vector<int32_t> key_nq, key_m2;
     std::vector<int32_t> key_off;   // nk + 1
+    // [first, last) determinant of the key (Nq, 2M), empty for none, at
+    // 2 ((Nq - kmap_nq0) kmap_m2 + (2M - kmap_m20) / 2)
+    std::vector<int32_t> kmap;
+    int kmap_nq0 = 0, kmap_m20 = 0, kmap_nq = 0, kmap_m2 = 0;
     std::vector<uint64_t> sd;       // nsd * W
     std::vector<int32_t> sd_key;    // nsd
     int nk() const { return (int)key_nq.size(); }
@@ -167,7 +171,6 @@ struct HostBasis {
 // Arguments of the device partner-list kernels (basis_kernels.hip), one species.
 struct PartnerArgs {
     const uint64_t* sd;      // [nsd][W]
-    const uint64_t* sdT;     // [W][nsd] (word-major copy for coalesced candidate loads)
     const int32_t* sd_key;   // [nsd]
     const int32_t* key_off;  // [nk + 1]
     const int32_t* key_nq;   // [nk]
@@ -181,7 +184,11 @@ struct PartnerArgs {
     int32_t* segT1;  // [nk + 1][nsd]
     int32_t* segT12;
     int32_t* self12;
+    const int32_t* orb_qn;   // [nsps] n | l << 8 | 2j << 16 | (2m + 64) << 24 of each orbit
+    const int32_t* kmap;     // [kmap_nq][kmap_m2][2] determinants of key (Nq, 2M): first, end
     int32_t nsd, nk, W;
+    int32_t nsps, budget;    // orbits; largest Nq of a determinant
+    int32_t kmap_nq0, kmap_m20, kmap_nq, kmap_m2;
 };
 
 // host_basis.cpp

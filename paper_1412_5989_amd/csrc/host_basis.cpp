@@ -190,6 +190,19 @@ int make_determinants(HostBasis& hb, std::string& err)
             }
             sp.key_off[k + 1] = (int32_t)tot;
         }
+        if (nk > 0) {
+            const auto mm = std::minmax_element(sp.key_m2.begin(), sp.key_m2.end());
+            sp.kmap_nq0 = sp.key_nq.front();
+            sp.kmap_m20 = *mm.first;
+            sp.kmap_nq = sp.key_nq.back() - sp.kmap_nq0 + 1;
+            sp.kmap_m2 = (*mm.second - *mm.first) / 2 + 1;  // 2M has the parity of X
+            sp.kmap.assign((size_t)2 * sp.kmap_nq * sp.kmap_m2, 0);
+            for (int k = 0; k < nk; k++) {
+                const size_t c = (size_t)(sp.key_nq[k] - sp.kmap_nq0) * sp.kmap_m2 + (sp.key_m2[k] - sp.kmap_m20) / 2;
+                sp.kmap[2 * c] = sp.key_off[k];
+                sp.kmap[2 * c + 1] = sp.key_off[k + 1];
+            }
+        }
         const int W = hb.W;
         sp.sd.resize((size_t)sp.key_off[nk] * W);
         sp.sd_key.resize(sp.key_off[nk]);
