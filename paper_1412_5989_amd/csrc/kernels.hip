@@ -210,18 +210,20 @@ __device__ __forceinline__ int seg_search(const int32_t* a, int n, int x)
 
 // Table position of V_{ab,cd} of class cls (0 pp, 1 pn, 2 nn) with
 // species-local orbits, for ordered pairs (a < b and c < d for pp and nn; a,
-// c protons and b, d neutrons for pn).  -1 if a pair is outside the table.
+// c protons and b, d neutrons for pn) that two determinants of the basis hold
+// with the same spectators.  Such pairs are always in the table and in one
+// sector: the spectators leave a pair at most the quanta that the table covers,
+// and the two determinants agree in 2M, parity and charge.  base(r) does not
+// decrease with r, so base(min(r, q)) + max(r, q) needs no comparison of r, q.
 __device__ __forceinline__ int tb_pos(const BasisDev& B, int cls, int a, int b, int c, int d)
 {
     // 32-bit unsigned offsets from the table's base (an SGPR pair): the loads
-    // take their address as base + offset with no 64-bit arithmetic per lane
-    const uint32_t n = (uint32_t)B.nsps, o = (uint32_t)cls * n * n;
-    const uint64_t e1 = ld32(B.pair, o + (uint32_t)a * n + (uint32_t)b);
-    const uint64_t e2 = ld32(B.pair, o + (uint32_t)c * n + (uint32_t)d);
-    const uint32_t l1 = (uint32_t)e1, l2 = (uint32_t)e2;
-    if (e1 == kNoPair64 || e2 == kNoPair64 || (l1 >> 16) != (l2 >> 16)) return -1;
-    const bool first = (l1 & 0xffff) <= (l2 & 0xffff);
-    return (int)((first ? (uint32_t)(e1 >> 32) : (uint32_t)(e2 >> 32)) + (first ? (l2 & 0xffff) : (l1 & 0xffff)));
+    // take their address as base + offset with no 64-bit arithmetic per lane;
+    // 24-bit products (3 n^2 < 2^24) at a quarter of the cost of 32-bit ones
+    const uint32_t n = (uint32_t)B.nsps, o = __umul24((uint32_t)cls, __umul24(n, n));
+    const uint64_t e1 = ld32(B.pair, __umul24((uint32_t)a, n) + (uint32_t)b + o);
+    const uint64_t e2 = ld32(B.pair, __umul24((uint32_t)c, n) + (uint32_t)d + o);
+    return (int)(min((uint32_t)(e1 >> 32), (uint32_t)(e2 >> 32)) + max((uint32_t)e1 & 0xffff, (uint32_t)e2 & 0xffff));
 }
 
 // Same for pairs in any order: each swap inside a pp or nn pair flips the sign.
@@ -397,15 +399,12 @@ __device__ __forceinline__ double kinetic_offdiag(const BasisDev& B, int p, int 
 }
 
 // The u-th two-body term of a queued entry: table position and sign.
-// The u-th term: table position (or -1) and sign; *ob receives the one-body
-// value of the kinetic term (0 for two-body terms).
-__device__ __forceinline__ int queued_term(const RowView& R, const WaveLds& L, uint32_t q, int u, bool* neg,
-                                           double* ob)
+// The u-th term: table position (-1 for the kinetic term, which is constant)
+// and sign.
+__device__ __forceinline__ int queued_term(const RowView& R, const WaveLds& L, uint32_t q, int u, bool* neg)
 {
-    *ob = 0.0;
     if (q_kind(q) != 0 && u == R.Z + R.NN - 1) {  // the kinetic term a+_p a_h
         *neg = q_neg(q);
-        *ob = kinetic_offdiag(*R.B, q_p(q), q_h(q));
         return -1;
     }
     const BasisDev& B = *R.B;
@@ -508,11 +507,13 @@ __device__ __forceinline__ int single_term(const RowView& R, const WaveLds& L, u
 // A queue that holds only one-nucleon differences (the walk treats the
 // diagonal on its own), each with the same number of terms nt = A - 1 (+1
 // with the kinetic term).  A round takes floor(64 / nt) entries and lane
-// k * nt + u takes term u of entry k.  Fill: the entry's first lane sums its nt
-// terms from LDS in order (FP64, rounded once).  Adjoint: every term lane adds
-// phase * G of its entry to the term's table position.  No search, one path.
+// k * nt + u takes term u of entry k; with nt > 64 a round is one entry and
+// lane u takes terms u, u + 64, ...  Fill: the entry's first lane sums its
+// lanes' terms from LDS in order (FP64, rounded once).  Adjoint: every term
+// lane adds phase * G of its entry to the term's table position.  No search,
+// one path.
 template <int MODE>
-__device__ void flush_singles(const RowView& R, WaveLds& L, int qn)
+__device__ __forceinline__ void flush_singles(const RowView& R, WaveLds& L, int qn)
 {
     const int lane = threadIdx.x & 63;
     const int nt = R.Z + R.NN - 1 + R.B->kinetic;
@@ -525,39 +526,35 @@ __device__ void flush_singles(const RowView& R, WaveLds& L, int qn)
         wave_sync();
         return;
     }
-    const int per = 64 / nt;
+    const int per = nt < 64 ? 64 / nt : 1;
     const float inv = 1.0f / (float)nt;
-    const int k = (int)(((float)lane + 0.5f) * inv);  // exact: the fraction stays >= 0.5 / 64 from an integer
-    const int u = lane - k * nt;
+    const int k = nt < 64 ? (int)(((float)lane + 0.5f) * inv) : 0;  // exact: the fraction stays >= 0.5 / 64 from an integer
     for (int q0 = 0; q0 < qn; q0 += per) {
         const int q = q0 + k;
         const bool act = k < per && q < qn;
-        if (MODE == kAdjoint) {
-            if (act) {
-                bool neg;
-                double ob;
-                const int kk = single_term(R, L, L.qrec[q], u, &neg, &ob);
-                const int64_t p = R.pos0 + L.qpos[q];
-                if (kk >= 0 && p < R.cap) {
-                    const float g = glb(R.gval)[p];
-                    adj_add(R, kk, neg ? -g : g);
-                }
-            }
-            continue;
-        }
         double v = 0.0;
         if (act) {
-            bool neg;
-            double ob;
-            const int kk = single_term(R, L, L.qrec[q], u, &neg, &ob);
-            const double x = kk >= 0 ? (double)glb(R.tbme)[kk] : ob;
-            v = neg ? -x : x;
+            const uint32_t rec = L.qrec[q];
+            const int64_t p = R.pos0 + L.qpos[q];
+            const float g = (MODE == kAdjoint && p < R.cap) ? glb(R.gval)[p] : 0.0f;
+            for (int u = lane - k * nt; u < nt; u += 64) {
+                bool neg;
+                double ob;
+                const int kk = single_term(R, L, rec, u, &neg, &ob);
+                if (MODE == kAdjoint) {
+                    if (kk >= 0 && p < R.cap) adj_add(R, kk, neg ? -g : g);
+                } else {
+                    const double x = kk >= 0 ? (double)glb(R.tbme)[kk] : ob;
+                    v += neg ? -x : x;
+                }
+            }
         }
+        if (MODE == kAdjoint) continue;
         L.tsum[lane] = v;
         wave_sync();
-        if (act && u == 0) {
+        if (act && lane == k * nt) {
             double sum = 0.0;
-            for (int i = 0; i < nt; i++) sum += L.tsum[lane + i];
+            for (int i = 0; i < nt && i < 64; i++) sum += L.tsum[lane + i];
             const int64_t p = R.pos0 + L.qpos[q];
             if (p < R.cap) glbw(R.val)[p] = (float)sum;
         }
@@ -565,125 +562,63 @@ __device__ void flush_singles(const RowView& R, WaveLds& L, int qn)
     }
 }
 
-// Evaluate (fill) or scatter (adjoint) the queued multi-term entries.
-// SINGLES: the queue holds no diagonal entry (the walk's own queue).
-template <int MODE, bool SINGLES>
+// Scatter the queued multi-term entries (diagonal or one nucleon moved) of the
+// adjoint that reads stored words.
 __device__ void flush_queue(const RowView& R, WaveLds& L, int qn)
 {
     const int lane = threadIdx.x & 63;
     if (qn == 0) return;
-    if (SINGLES && R.Z + R.NN - 1 + R.B->kinetic <= 64) {
-        flush_singles<MODE>(R, L, qn);
-        return;
-    }
     // first term of each queued entry
     int tot = 0;
     for (int base = 0; base < qn; base += 64) {
         const int q = base + lane;
         const int t = q < qn ? queued_terms(R, L.qrec[q]) : 0;
-        if (MODE == kFill && q < qn && t == 0) {
-            // no terms (a single nucleon): the diagonal is its single-particle
-            // energy, a one-nucleon difference is 0
-            const int64_t p = R.pos0 + L.qpos[q];
-            if (p < R.cap) glbw(R.val)[p] = q_kind(L.qrec[q]) == 0 ? (float)R.spe_sum : 0.0f;
-        }
         const int incl = wave_incl_scan(t);
         if (q < kQueue) L.toff[q + 1] = tot + incl;
         if (lane == 0 && base == 0) L.toff[0] = 0;
         tot += lane63(incl);
     }
     wave_sync();
-    double carry = 0.0;
-    int carry_q = -1;
     for (int t0 = 0; t0 < tot; t0 += 64) {
         const int t = t0 + lane;
-        const bool act = t < tot;
-        int q = 0;
-        double v = 0.0;
-        if (act) {
-            q = seg_search(L.toff, qn, t);
+        if (t < tot) {
+            const int q = seg_search(L.toff, qn, t);
             bool neg;
-            double ob;
-            const int k = queued_term(R, L, L.qrec[q], t - L.toff[q], &neg, &ob);
-            if (MODE == kFill && k < 0) v = neg ? -ob : ob;
-            if (k >= 0) {
-                if (MODE == kFill) {
-                    const double x = (double)glb(R.tbme)[k];
-                    v = neg ? -x : x;
-                } else {
-                    const int64_t p = R.pos0 + L.qpos[q];
-                    if (p < R.cap) {
-                        const float g = glb(R.gval)[p];
-                        adj_add(R, k, neg ? -g : g);
-                    }
-                }
+            const int k = queued_term(R, L, L.qrec[q], t - L.toff[q], &neg);
+            const int64_t p = R.pos0 + L.qpos[q];
+            if (k >= 0 && p < R.cap) {
+                const float g = glb(R.gval)[p];
+                adj_add(R, k, neg ? -g : g);
             }
-        }
-        if (MODE == kFill) {
-            // segmented inclusive scan over the lanes, keyed by q, fixed order
-            const int qq = act ? q : 0x7fffffff;
-            for (int o = 1; o < 64; o <<= 1) {
-                const double vu = __shfl_up(v, o, 64);
-                const int qu = __shfl_up(qq, o, 64);
-                if (lane >= o && qu == qq) v += vu;
-            }
-            if (act && q == carry_q) v += carry;
-            const int qnext = __shfl_down(qq, 1, 64);
-            if (act && (lane == 63 || qnext != qq) && t == L.toff[q + 1] - 1) {
-                // the entry's last term: write it
-                const int64_t p = R.pos0 + L.qpos[q];
-                double x = v;
-                if (q_kind(L.qrec[q]) == 0) x += R.spe_sum;
-                if (p < R.cap) glbw(R.val)[p] = (float)x;
-            }
-            // an entry cut by the end of the round continues in the next one
-            carry = __shfl(v, 63, 64);
-            carry_q = __shfl(qq, 63, 64);
         }
     }
     wave_sync();
 }
 
 // The row's diagonal entry: fill, its value, the single-particle sum plus every
-// occupied pair V_{ab,ab} (pp, nn, pn), one lane per pair, summed in FP64 in a
-// fixed order and rounded once; adjoint, G of the entry added to every
-// occupied pair's table position.  Lane u < Z(Z-1)/2 takes proton pair u in
-// colex order (u = y(y-1)/2 + x, x < y), the next N(N-1)/2 lanes the neutron
-// pairs, the last Z*N lanes the proton-neutron pairs.
+// occupied pair V_{ab,ab}, one lane per pair, summed in FP64 in a fixed order
+// and rounded once; adjoint, G of the entry added to every occupied pair's
+// table position.  Lane u takes pair u of the A nucleons (protons, then
+// neutrons) in colex order (u = y(y-1)/2 + x, x < y).
 template <int MODE>
 __device__ void row_diagonal(const RowView& R, const WaveLds& L, int64_t p)
 {
     const int lane = threadIdx.x & 63;
     const BasisDev& B = *R.B;
     const int Z = R.Z, NN = R.NN;
-    const int npp = Z * (Z - 1) / 2, nnn = NN * (NN - 1) / 2, tot = npp + nnn + Z * NN;
+    const int tot = (Z + NN) * (Z + NN - 1) / 2;
     const float g = (MODE == kAdjoint && p < R.cap) ? glb(R.gval)[p] : 0.0f;
     double acc = 0.0;
     for (int u0 = 0; u0 < tot; u0 += 64) {
         const int u = u0 + lane;
         if (u < tot) {
-            int cls, a, b;
-            if (u < npp + nnn) {
-                const bool pp = u < npp;
-                const int t = pp ? u : u - npp;
-                int y = (int)(0.5f * (1.0f + sqrtf(1.0f + 8.0f * (float)t)));
-                while (y * (y - 1) / 2 > t) y--;
-                while ((y + 1) * y / 2 <= t) y++;
-                const int x = t - y * (y - 1) / 2;
-                const uint8_t* o = pp ? L.occ : L.occ + Z;
-                a = o[x];
-                b = o[y];
-                cls = pp ? 0 : 2;
-            } else {
-                const int t = u - npp - nnn;
-                const int ia = t / NN;
-                a = L.occ[ia];
-                b = L.occ[Z + (t - ia * NN)];
-                cls = 1;
-            }
-            const int k = tb_pos(B, cls, a, b, a, b);
-            if (MODE == kFill && k >= 0) acc += (double)glb(R.tbme)[k];
-            if (MODE == kAdjoint && k >= 0 && p < R.cap) adj_add(R, k, g);
+            int y = (int)(0.5f * (1.0f + sqrtf(1.0f + 8.0f * (float)u)));
+            if (y * (y - 1) / 2 > u) y--;  // u < 2^12: the root is off by one rounding at most
+            else if ((y + 1) * y / 2 <= u) y++;
+            const int x = u - y * (y - 1) / 2;
+            const int k = tb_pos(B, y < Z ? 0 : (x < Z ? 1 : 2), L.occ[x], L.occ[y], L.occ[x], L.occ[y]);
+            if (MODE == kFill) acc += (double)glb(R.tbme)[k];
+            if (MODE == kAdjoint && p < R.cap) adj_add(R, k, g);
         }
     }
     if (MODE == kFill) {
@@ -692,23 +627,23 @@ __device__ void row_diagonal(const RowView& R, const WaveLds& L, int64_t p)
     }
 }
 
-// Occupied orbits of row (gP, gN) into L.occ, for the multi-term entries:
-// lane j < 2W holds determinant word j (protons, then neutrons), a wave scan
-// gives each word's first slot in occ, and (spe: for the fill's values) the
-// shells of the occupied orbits give the single-particle sum.
+// Occupied orbits of row (gP, gN) into L.occ, for the multi-term entries: bit
+// `lane` of each determinant word (protons, then neutrons) goes to the slot
+// that the bits before it leave, and (spe: for the fill's values) the shells of
+// the occupied orbits give the single-particle sum.
 __device__ void row_occ(const BasisDev& B, WaveLds& L, RowView& R, int gP, int gN, bool spe)
 {
     const int lane = threadIdx.x & 63;
     const SpeciesDev& SP = B.sp[0];
     const SpeciesDev& SN = B.sp[1];
     const int W = B.W;
-    uint64_t word = 0;
-    if (lane < 2 * W)
-        word = lane < W ? glb(SP.sd)[(int64_t)gP * W + lane] : glb(SN.sd)[(int64_t)gN * W + (lane - W)];
-    const int cnt = __popcll(word);
-    int t = wave_incl_scan(cnt) - cnt;
-    const int obase = (lane < W ? lane : lane - W) * 64;
-    for (uint64_t x = word; x; x &= x - 1) L.occ[t++] = (uint8_t)(obase + __ffsll((long long)x) - 1);
+    int n = 0;
+    for (int j = 0; j < 2 * W; j++) {
+        const uint64_t word = j < W ? cst(SP.sd)[(int64_t)gP * W + j] : cst(SN.sd)[(int64_t)gN * W + (j - W)];
+        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(word >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)word, 0));
+        if (__builtin_amdgcn_inverse_ballot_w64(word)) L.occ[n + before] = (uint8_t)((j < W ? j : j - W) * 64 + lane);
+        n += __popcll(word);
+    }
     wave_sync();
     if (!spe) return;
     const int A = R.Z + R.NN;
@@ -745,40 +680,62 @@ __device__ void do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView& R)
     const gptr<int32_t> sN1 = glb(SN.seg1 + (int64_t)gN * (nkn + 1));
     const gptr<int32_t> sN12 = glb(SN.seg12 + (int64_t)gN * (nkn + 1));
     const int self12 = uniform(cst(SN.self12)[gN]);
+    const int self = uniform(cst(SN.seg12 + (int64_t)gN * (nkn + 1))[kn]) + self12;  // N in l12(N)
 
     row_occ(B, L, R, gP, gN, MODE == kFill);
 
-    int64_t pos = 0;  // entries of the row so far
+    // One loop over the rounds of 64 entries; a round that finds its chunk of
+    // segments used up first takes the next chunk, or the next window of
+    // blocks.  (Nested loops with a second flush of the queue at the end hold
+    // every invariant of both flushes in scalar registers, which then spill.)
     int qn = 0;       // queued multi-term entries
     int diag_at = -1; // position of the diagonal entry in the row
-    for (int w0 = R.full ? 0 : bi; w0 < B.nblk; w0 += 64) {
-        // 1. lane t: target block w0 + t of the window: proton partners of P,
-        //    the row's neutron partners, column base
-        const int b2 = w0 + lane;
-        int np = 0, bp = 0, bcol = 0, bstr = 0, bn1 = 0, bl1 = 0, bn12 = 0, bl12 = 0;
-        if (b2 < B.nblk) {
-            const i32x4 bk = glb((const i32x4*)B.blk)[b2];  // one 16-byte load
-            const int kp2 = bk.x, kn2 = bk.y;
-            const bool same_n = (kn2 == kn);
-            const int ps = same_n ? sP12[kp2] : sP1[kp2];
-            np = (same_n ? sP12[kp2 + 1] : sP1[kp2 + 1]) - ps;
-            bp = ps | (same_n ? (int)0x80000000 : 0);
-            bcol = bk.z;  // first row of the block
-            bstr = bk.w;  // |Kn'|
-            bn1 = sN1[kn2];
-            bl1 = sN1[kn2 + 1] - bn1;
-            bn12 = sN12[kn2] + (b2 == bi && !R.full ? self12 : 0);  // diagonal block: N' >= N
-            bl12 = sN12[kn2 + 1] - bn12;
-            // a block with another neutron key needs a neutron partner of N in it
-            // (d <= 1 for a moved proton, d <= 2 for P' = P): otherwise every
-            // segment of the block is empty
-            if (!same_n && bl1 == 0 && (kp2 != kp || bl12 == 0)) np = 0;
-        }
-        const int bincl = wave_incl_scan(np);
-        const int bstart = bincl - np;  // first segment of the lane's block
-        const int S = lane63(bincl);
-        int bcarry = -1;
-        for (int s0 = 0; s0 < S; s0 += 64) {
+    // window of 64 target blocks from w0, lane t: block w0 + t
+    int w0 = (R.full ? 0 : bi) - 64, S = 0, bcarry = -1;
+    int np = 0, bp = 0, bcol = 0, bstr = 0, bn1 = 0, bl1 = 0, bn12 = 0, bl12 = 0, bstart = 0;
+    // chunk of 64 segments that ends before s0, lane j: its segment
+    int s0 = 0, T = 0, ecarry = -1, lim = 0;
+    int len = 0, so = 0, sc = 0, estart = 0;
+    uint64_t pr = 0;
+    int pos = 0, cpos = 0;  // entries of the row so far, at the start of the chunk
+    int64_t base = R.pos0;  // first entry of the chunk: per-lane offsets from it stay 32-bit
+    int e0 = 0;             // first entry of the round in the chunk
+    bool more = true;
+    for (;;) {
+        while (e0 >= T) {
+            if (s0 >= S) {
+                w0 += 64;
+                more = w0 < B.nblk;
+                if (!more) break;
+                // 1. lane t: target block w0 + t of the window: proton partners of P,
+                //    the row's neutron partners, column base
+                const int b2 = w0 + lane;
+                np = bl1 = bl12 = 0;
+                if (b2 < B.nblk) {
+                    const i32x4 bk = glb((const i32x4*)B.blk)[b2];  // one 16-byte load
+                    const int kp2 = bk.x, kn2 = bk.y;
+                    const bool same_n = (kn2 == kn);
+                    const int ps = same_n ? sP12[kp2] : sP1[kp2];
+                    np = (same_n ? sP12[kp2 + 1] : sP1[kp2 + 1]) - ps;
+                    bp = ps | (same_n ? (int)0x80000000 : 0);
+                    bcol = bk.z;  // first row of the block
+                    bstr = bk.w;  // |Kn'|
+                    bn1 = sN1[kn2];
+                    bl1 = sN1[kn2 + 1] - bn1;
+                    bn12 = sN12[kn2] + (b2 == bi && !R.full ? self12 : 0);  // diagonal block: N' >= N
+                    bl12 = sN12[kn2 + 1] - bn12;
+                    // a block with another neutron key needs a neutron partner of N in it
+                    // (d <= 1 for a moved proton, d <= 2 for P' = P): otherwise every
+                    // segment of the block is empty
+                    if (!same_n && bl1 == 0 && (kp2 != kp || bl12 == 0)) np = 0;
+                }
+                const int bincl = wave_incl_scan(np);
+                bstart = bincl - np;  // first segment of the lane's block
+                S = lane63(bincl);
+                s0 = 0;
+                bcarry = -1;
+                continue;
+            }
             // 2. lane j: segment s0 + j = (target block, P'): its entry count
             const int s = s0 + lane;
             clear_marks(L);
@@ -787,9 +744,7 @@ __device__ void do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView& R)
             const int t_col = lane_read(bcol, t), t_str = lane_read(bstr, t);
             const int t_n1 = lane_read(bn1, t), t_l1 = lane_read(bl1, t);
             const int t_n12 = lane_read(bn12, t), t_l12 = lane_read(bl12, t);
-            int len = 0;
-            uint64_t pr = 0;
-            int so = 0, sc = 0;
+            len = 0;
             if (s < S) {
                 const int q = (t_bp & 0x7fffffff) + s - t_start;
                 pr = t_bp < 0 ? P12[(uint32_t)q] : P1[(uint32_t)q];
@@ -798,7 +753,8 @@ __device__ void do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView& R)
                 if (w0 + t == bi && ipp < ip && !R.full) {
                     len = 0;  // lower triangle
                 } else if (dp == 2) {
-                    len = 1;  // two protons moved: N' = N
+                    len = 1;  // two protons moved: N' = N, the record of N itself
+                    so = self | (int)0x80000000;
                 } else if (dp == 1) {
                     so = t_n1;
                     len = t_l1;
@@ -808,90 +764,82 @@ __device__ void do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView& R)
                 }
             }
             const int eincl = wave_incl_scan(len);
-            const int T = lane63(eincl);
-            const int estart = eincl - len;  // first entry of the lane's segment
-            // 3. the entries of the chunk, 64 consecutive ones per round
+            T = lane63(eincl);
+            estart = eincl - len;  // first entry of the lane's segment
             clear_marks(L);
-            int ecarry = -1;
-            // entries of this chunk of segments start at row position pos:
-            // per-lane offsets from uniform bases stay 32-bit
-            const int64_t base = R.pos0 + pos;
-            const int room = (int)max((int64_t)0, min(R.cap - base, (int64_t)0x7fffffff));
-            for (int e0 = 0; e0 < T; e0 += 64) {
-                const int e = e0 + lane;
-                const int j = owner_of(L, estart, len, e0, &ecarry);
-                const uint64_t prj = lane_read64(pr, j);
-                const int so2 = lane_read(so, j), sc2 = lane_read(sc, j), k = e - lane_read(estart, j);
-                bool special = false;
-                uint32_t qr = 0;
-                if (e < T) {
-                    const int dp = rec_d(prj);
-                    uint64_t nr = 0;
-                    if (dp != 2) {
-                        const uint32_t idx = (uint32_t)((so2 & 0x7fffffff) + k);
-                        nr = so2 < 0 ? N12[idx] : N1[idx];
-                    }
-                    const int dn = rec_d(nr);
-                    special = (dp != 2) && (dp + dn != 2);
-                    // two nucleons moved: pp (proton record), pn (both), nn (neutron record)
-                    const int cls = dp == 2 ? 0 : (dp == 1 ? 1 : 2);
-                    const int a = dp == 0 ? rec_p1(nr) : rec_p1(prj);
-                    const int b = dp == 2 ? rec_p2(prj) : (dp == 1 ? rec_p1(nr) : rec_p2(nr));
-                    const int c = dp == 0 ? rec_h1(nr) : rec_h1(prj);
-                    const int d = dp == 2 ? rec_h2(prj) : (dp == 1 ? rec_h1(nr) : rec_h2(nr));
-                    const bool neg = rec_neg(prj) ^ rec_neg(nr);
-                    const bool inb = e < room;
-                    const uint32_t ue = (uint32_t)e;
-                    // upstream value first: its load overlaps the table lookup
-                    const float gv = (MODE == kAdjoint && !special && inb) ? ld32(R.gval + base, ue) : 0.0f;
-                    const int key = special ? -1 : tb_pos(B, cls, a, b, c, d);
-                    if (inb) {
-                        if (MODE == kFill) {
-                            st32(R.col + base, ue, (int32_t)(sc2 + (dp == 2 ? in : rec_local(nr))));
-                            if (!special) {
-                                const float x = key >= 0 ? ld32(R.tbme, (uint32_t)key) : 0.0f;
-                                st32(R.val + base, ue, neg ? -x : x);
-                            }
-                        } else if (key >= 0) {
-                            adj_add(R, key, neg ? -gv : gv);
-                        }
-                    }
-                    if (special) {
-                        // queued: the moved nucleon's orbits and phase, or the diagonal
-                        const uint64_t mr = dp == 1 ? prj : nr;
-                        const uint32_t kind = dp == 1 ? 1u : (dn == 1 ? 2u : 0u);
-                        qr = kind | ((uint32_t)rec_h1(mr) << 8) | ((uint32_t)rec_p1(mr) << 16) |
-                             ((uint32_t)rec_neg(mr) << 24);
-                    }
-                    if (MODE == kFill && R.keys && inb)
-                        st32(R.keys + base, ue, special ? (kKeySpecial | qr)
-                                                        : (key >= 0 ? ((uint32_t)key | (neg ? kKeyNeg : 0u)) : kKeyNone));
-                }
-                // the diagonal entry (nothing moved) is treated on its own
-                const bool diag = special && q_kind(qr) == 0;
-                const uint64_t md = __ballot(diag);
-                if (md) diag_at = __builtin_amdgcn_readlane((int)(pos + e), __ffsll((long long)md) - 1);
-                special = special && !diag;
-                const uint64_t m = __ballot(special);
-                if (m) {
-                    const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-                    if (special) {
-                        L.qpos[qn + rank] = (int32_t)(pos + e);
-                        L.qrec[qn + rank] = qr;
-                    }
-                    qn += __popcll(m);
-                    wave_sync();
-                    if (qn > kQueue - 64) {  // room for one more round
-                        flush_queue<MODE, true>(R, L, qn);
-                        qn = 0;
-                    }
-                }
-            }
+            ecarry = -1;
+            cpos = pos;
+            base = R.pos0 + cpos;
+            lim = (int)max((int64_t)0, min(R.cap - base, (int64_t)T));
             pos += T;
+            s0 += 64;
+            e0 = 0;
         }
+        if (!more || qn > kQueue - 64) {  // the end, or no room for one more round
+            if (qn > 0) flush_singles<MODE>(R, L, qn);
+            qn = 0;
+            if (!more) break;
+        }
+        // 3. 64 consecutive entries of the chunk
+        const int e = e0 + lane;
+        const int j = owner_of(L, estart, len, e0, &ecarry);
+        const uint64_t prj = lane_read64(pr, j);
+        // lanes past the last entry repeat it, so that every lane of
+        // the round runs the same code on valid records
+        const int so2 = lane_read(so, j), sc2 = lane_read(sc, j);
+        const uint32_t idx = (uint32_t)((so2 & 0x7fffffff) + min(e, T - 1) - lane_read(estart, j));
+        const uint64_t nr = (so2 < 0 ? N12 : N1)[idx];
+        const uint32_t ph = (uint32_t)(prj >> 32), nh = (uint32_t)(nr >> 32), nl = (uint32_t)nr;
+        const int dp = (int)((ph >> 25) & 3), dn = (int)((nh >> 25) & 3);
+        // two nucleons moved: pp (proton record), pn (both), nn (neutron record)
+        const bool two = dp + dn == 2, pn = dp == 1;
+        const uint32_t xh = dp == 0 ? nh : ph, xl = dp == 0 ? nl : (uint32_t)prj;
+        const int a = xh & 255, b = pn ? nh & 255 : (xh >> 16) & 255;
+        const int c = xl >> 24, d = pn ? nl >> 24 : (xh >> 8) & 255;
+        const bool neg = ((ph ^ nh) >> 24) & 1;
+        const bool special = e < T && !two;
+        const bool inb = e < lim;
+        const uint32_t ue = (uint32_t)e;
+        uint32_t qr = 0;
+        if (inb && two) {
+            // upstream value first: its load overlaps the table lookup
+            const float gv = MODE == kAdjoint ? ld32(R.gval + base, ue) : 0.0f;
+            const int key = tb_pos(B, 2 - dp, a, b, c, d);
+            if (MODE == kFill) {
+                const float x = ld32(R.tbme, (uint32_t)key);
+                st32(R.val + base, ue, neg ? -x : x);
+                if (R.keys) st32(R.keys + base, ue, (uint32_t)key | (neg ? kKeyNeg : 0u));
+            } else {
+                adj_add(R, key, neg ? -gv : gv);
+            }
+        }
+        if (MODE == kFill && inb) st32(R.col + base, ue, sc2 + (int)(nl & kRecLocalMask));
+        if (special) {
+            // queued: the moved nucleon's orbits and phase, or the diagonal
+            const uint64_t mr = pn ? prj : nr;
+            const uint32_t kind = pn ? 1u : (dn == 1 ? 2u : 0u);
+            qr = kind | ((uint32_t)rec_h1(mr) << 8) | ((uint32_t)rec_p1(mr) << 16) |
+                 ((uint32_t)rec_neg(mr) << 24);
+            if (MODE == kFill && R.keys && inb) st32(R.keys + base, ue, kKeySpecial | qr);
+        }
+        // the diagonal entry (nothing moved) is treated on its own
+        const bool diag = special && q_kind(qr) == 0;
+        const uint64_t md = __ballot(diag);
+        if (md) diag_at = __builtin_amdgcn_readlane((int)(cpos + e), __ffsll((long long)md) - 1);
+        const bool queued = special && !diag;
+        const uint64_t m = __ballot(queued);
+        if (m) {
+            const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            if (queued) {
+                L.qpos[qn + rank] = (int32_t)(cpos + e);
+                L.qrec[qn + rank] = qr;
+            }
+            qn += __popcll(m);
+            wave_sync();
+        }
+        e0 += 64;
     }
-    flush_queue<MODE, true>(R, L, qn);
     if (diag_at >= 0) row_diagonal<MODE>(R, L, R.pos0 + diag_at);
 }
 
@@ -937,12 +885,12 @@ __device__ void do_row_keys(const BasisDev& B, WaveLds& L, int bi, int r, RowVie
             qn += __popcll(m);
             wave_sync();
             if (qn > kQueue - 64) {  // room for one more round
-                flush_queue<kAdjoint, false>(R, L, qn);
+                flush_queue(R, L, qn);
                 qn = 0;
             }
         }
     }
-    flush_queue<kAdjoint, false>(R, L, qn);
+    flush_queue(R, L, qn);
 }
 
 // Block of item u of a list of items per block (global block list): the
@@ -959,7 +907,7 @@ __device__ __forceinline__ int block_of(const int64_t* off, int nblocks, int64_t
 }
 
 // Row i of basis B, row r of its block bi.
-template <int MODE>
+template <int MODE, bool KEYS>
 __device__ __forceinline__ void run_row_at(const BasisDev& B, int bi, int i, int r, const float* __restrict__ tbme,
                                            const int64_t* __restrict__ row_ptr, int64_t nrp, int32_t* __restrict__ col,
                                            float* __restrict__ val, const float* __restrict__ gval,
@@ -987,7 +935,7 @@ __device__ __forceinline__ void run_row_at(const BasisDev& B, int bi, int i, int
     R.full = full;
     R.pos0 = uniform64(cst(row_ptr)[B.row0 + i]);
     R.cap = uniform64(cst(row_ptr)[nrp - 1]);  // the entries of all bases end here
-    if (MODE == kAdjoint && keys)
+    if constexpr (KEYS)
         do_row_keys(B, L, bi, r, R, uniform64(cst(row_ptr)[B.row0 + i + 1]));
     else
         do_row<MODE>(B, L, bi, r, R);
@@ -1004,7 +952,7 @@ __device__ __forceinline__ void fill_row(const BasisDev* __restrict__ bases, con
     const int gb = block_of(row_off, nblocks, g);
     const BasisDev& B = bases[uniform(cst(blk_basis)[gb])];
     const int bi = uniform(cst(blk_local)[gb]), r = uniform((int)(g - cst(row_off)[gb]));
-    run_row_at<kFill>(B, bi, uniform((int)cst(B.blk_off)[bi]) + r, r, tbme, row_ptr, nrp, col, val, nullptr, nullptr,
+    run_row_at<kFill, false>(B, bi, uniform((int)cst(B.blk_off)[bi]) + r, r, tbme, row_ptr, nrp, col, val, nullptr, nullptr,
                       nullptr, nullptr, false, 0, 0, full, keys, L);
 }
 
@@ -1025,25 +973,25 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
     __shared__ WaveLds lds[WAVES];
     const int wid = uniform(threadIdx.x >> 6);
     const int64_t nrows = uniform64(cst(row_off)[nblocks]);
-    if (grab <= 0) {
-        const int64_t wg = xcd ? xcd_contiguous(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
-        const int64_t g = wg * WAVES + wid;
-        if (g < nrows)
-            fill_row(bases, blk_basis, blk_local, nblocks, row_off, g, tbme, row_ptr, nrp, col, val, full != 0, keys,
-                     lds[wid]);
-        return;
-    }
     for (;;) {
-        unsigned long long t = 0;
-        if ((threadIdx.x & 63) == 0)
-            t = __hip_atomic_fetch_add(glbw(queue), (unsigned long long)grab, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t g0 = uniform64((int64_t)t);
-        if (g0 >= nrows) break;
-        const int64_t g1 = g0 + grab < nrows ? g0 + grab : nrows;
+        int64_t g0, g1;
+        if (grab <= 0) {
+            const int64_t wg = xcd ? xcd_contiguous(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+            g0 = wg * WAVES + wid;
+            g1 = g0 + 1;
+        } else {
+            unsigned long long t = 0;
+            if ((threadIdx.x & 63) == 0)
+                t = __hip_atomic_fetch_add(glbw(queue), (unsigned long long)grab, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+            g0 = uniform64((int64_t)t);
+            g1 = g0 + grab;
+        }
+        if (g1 > nrows) g1 = nrows;
         for (int64_t g = g0; g < g1; g++)
             fill_row(bases, blk_basis, blk_local, nblocks, row_off, g, tbme, row_ptr, nrp, col, val, full != 0, keys,
                      lds[wid]);
+        if (grab <= 0 || g0 >= nrows) break;
     }
 }
 
@@ -1250,7 +1198,8 @@ __global__ void __launch_bounds__(256) tile_offsets(const BasisDev* __restrict__
 // takes tiles from the work counter *queue (zero at launch).  use_table == 0
 // (global table positions do not fit 32 bits): every contribution goes to
 // gacc and no record is written.
-template <int WAVES, int SLOT_BITS>
+// KEYS: from the words the fill stored, else by walking the partner lists.
+template <int WAVES, int SLOT_BITS, bool KEYS>
 __global__ void __launch_bounds__(64 * WAVES)
     adjoint_kernel(const BasisDev* __restrict__ bases, const int32_t* __restrict__ blk_basis,
                    const int32_t* __restrict__ blk_local, int nblocks, const int64_t* __restrict__ tile_off,
@@ -1327,7 +1276,7 @@ __global__ void __launch_bounds__(64 * WAVES)
             if (t >= cnt) break;
             const int u = t / tn, v = t - u * tn;
             const int r = (ip0 + u) * nKn + in0 + v;
-            run_row_at<kAdjoint>(B, bi, uniform((int)cst(B.blk_off)[bi] + r), r, nullptr, row_ptr, nrp,
+            run_row_at<kAdjoint, KEYS>(B, bi, uniform((int)cst(B.blk_off)[bi] + r), r, nullptr, row_ptr, nrp,
                                  nullptr, nullptr, gval, gacc, (lptr<uint32_t>)hkey, (lptr<int32_t>)hval,
                                  use_table != 0, SLOT_BITS, qshift, false, const_cast<uint32_t*>(keys), lds[wid]);
         }
@@ -1713,7 +1662,7 @@ __global__ void zero_u64(unsigned long long* __restrict__ p) { *p = 0; }
 // kind numbers the kernel for the per-device cache.
 static unsigned resident_blocks(const void* kernel, int threads, int kind)
 {
-    constexpr int kDevs = 64, kKinds = 8;
+    constexpr int kDevs = 64, kKinds = 9;
     static std::atomic<int> cache[kDevs][kKinds];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevs) dev = 0;
@@ -1811,26 +1760,20 @@ hipError_t launch_vjp(const BasisDev* bases, int nbases, const int32_t* blk_basi
         hipLaunchKernelGGL(tile_offsets, dim3(1), dim3(256), 0, s, bases, blk_basis, blk_local, nblocks, rows, tile_n,
                            tile_off, nbases, adjb);
         const bool wide = keys || t.adj_wide;  // 16 wavefronts, 16384-slot table
-        const void* kern = wide ? (const void*)adjoint_kernel<kAdjKeysWaves, kAdjKeysSlotBits>
-                                : (const void*)adjoint_kernel<kAdjWaves, kAdjSlotBits>;
+        const auto kern = keys   ? adjoint_kernel<kAdjKeysWaves, kAdjKeysSlotBits, true>
+                          : wide ? adjoint_kernel<kAdjKeysWaves, kAdjKeysSlotBits, false>
+                                 : adjoint_kernel<kAdjWaves, kAdjSlotBits, false>;
         const int threads = 64 * (wide ? kAdjKeysWaves : kAdjWaves);
         unsigned grid = (unsigned)ntiles;
         if (recs) hipLaunchKernelGGL(zero_u64, dim3(1), dim3(1), 0, s, rec_count);
         if (t.adj_persistent) {
             hipLaunchKernelGGL(zero_u64, dim3(1), dim3(1), 0, s, queue);
-            const unsigned res = resident_blocks(kern, threads, wide ? 7 : 6);
+            const unsigned res = resident_blocks((const void*)kern, threads, keys ? 7 : (wide ? 8 : 6));
             grid = res < grid ? res : grid;
         }
-        if (wide)
-            hipLaunchKernelGGL((adjoint_kernel<kAdjKeysWaves, kAdjKeysSlotBits>), dim3(grid), dim3(threads), 0, s,
-                               bases, blk_basis, blk_local, nblocks, tile_off, rows, tile_n, row_ptr, nrp, gval, keys,
-                               gacc, use_table, t.adj_persistent ? 1 : 0, queue, adjb, recs, rec_cap, rec_count,
-                               hist, gscale, t.row_xcd);
-        else
-            hipLaunchKernelGGL((adjoint_kernel<kAdjWaves, kAdjSlotBits>), dim3(grid), dim3(threads), 0, s, bases,
-                               blk_basis, blk_local, nblocks, tile_off, rows, tile_n, row_ptr, nrp, gval, keys, gacc,
-                               use_table, t.adj_persistent ? 1 : 0, queue, adjb, recs, rec_cap, rec_count, hist,
-                               gscale, t.row_xcd);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, s, bases, blk_basis, blk_local, nblocks, tile_off, rows,
+                           tile_n, row_ptr, nrp, gval, keys, gacc, use_table, t.adj_persistent ? 1 : 0, queue, adjb,
+                           recs, rec_cap, rec_count, hist, gscale, t.row_xcd);
     }
     if (ntbme > 0) {
         if (use_table && walked && recs && nbuckets > 0) {

@@ -46,3 +46,31 @@ def test_partner_lists(ci, p):
     assert np.array_equal(np.diff(r)[rows], o.row_counts(rows)), p
     got = np.concatenate([col[r[i]:r[i + 1]].cpu().numpy() for i in rows])
     assert np.array_equal(got, o.rows(rows, values=False)[1]), p
+
+
+# one-nucleon differences of more than 64 terms (A - 1, plus the kinetic term),
+# which no round of lanes holds at once: the walking adjoint against the one
+# from stored words (another evaluation of the same terms), and the fill against
+# the adjoint through <G, H(t) - H(0)> = <H^T G, t>
+@pytest.mark.parametrize("p", [(40, 39, 0, 1, -1), (39, 40, 0, 3, -1), (40, 26, 0, 18, 1)])
+@pytest.mark.parametrize("kinetic", [0, 1])
+def test_many_nucleons(ci, p, kinetic):
+    b = ci.ci_basis_build([p + (15.0, kinetic)])
+    rp, nnz = ci.ci_hamiltonian_count(b)
+    assert b.info[0]["dim"] > 1 and sum(nnz) > b.info[0]["dim"]
+    g = torch.Generator(device="cuda").manual_seed(11)
+    t = torch.randn(b.n_tbme, device="cuda", generator=g)
+    col, h0 = ci.ci_hamiltonian_fill(b, torch.zeros_like(t), rp)
+    col, h, keys = ci.ci_hamiltonian_fill_keys(b, t, rp)
+    G = torch.randn(sum(nnz), device="cuda", generator=g)
+    b.tuning = {"adj_rows": 32, "adj_tile_n": 8, "adjk_rows": 32, "adjk_tile_n": 8}
+    walk = ci.ci_hamiltonian_vjp(b, rp, G)
+    stored = ci.ci_hamiltonian_vjp_keys(b, rp, keys, G)
+    assert torch.equal(walk, stored)
+    lhs = float((G.double() * (h.double() - h0.double())).sum())
+    rhs = float((walk.double() * t.double()).sum())
+    # h and h0 are rounded to FP32; a gradient element is rounded to FP32 and
+    # sums at most dim contributions on a grid of spacing 2^-24 max |G|
+    tol = float((G.abs().double() * (h.abs() + h0.abs()).double()).sum()) * 2.0**-24
+    tol += float((t.abs().double() * (walk.abs().double() * 2.0**-24 + b.info[0]["dim"] * 2.0**-25 * float(G.abs().max()))).sum())
+    assert abs(lhs - rhs) <= tol
