@@ -137,8 +137,8 @@ typedef struct {
     int32_t adjk_persistent; /* adjoint from stored words: 0 one workgroup per tile, 1 persistent */
     int32_t row_xcd;        /* grids of rows or tiles (not persistent): 0 launch order; 1 each of the 8 XCDs */
                             /* (workgroup g runs on XCD g mod 8) takes one contiguous eighth of the grid   */
-    int32_t adj_wide;       /* walking adjoint: 0 8 wavefronts sharing a 4096-slot table (three workgroups */
-                            /* per CU); 1 16 wavefronts sharing a 16384-slot table (one per CU)            */
+    int32_t adj_wide;       /* walking adjoint: 0 8 wavefronts sharing a 4096-slot table (four workgroups  */
+                            /* per CU); 1 16 wavefronts sharing an 8192-slot table (two per CU)            */
     int32_t adj_flush;      /* both adjoints: 0 each tile writes its table as records, summed per bucket by */
                             /* a second kernel; 1 each tile adds its table to int64 accumulators (device   */
                             /* atomics), then one conversion to FP32                                        */

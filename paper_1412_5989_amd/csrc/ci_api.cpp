@@ -32,7 +32,7 @@ hipError_t launch_vjp(const BasisDev* bases, int nbases, const int32_t* blk_basi
                       float* gtbme, unsigned long long* gacc, uint64_t* recs, int64_t rec_cap,
                       unsigned long long* rec_count, int32_t* hist, int64_t ntbme, const ci_tuning& t,
                       unsigned long long* queue, unsigned long long* gscale, int64_t nnz_total, hipStream_t s);
-int adjoint_slots(bool wide);
+int adjoint_slots(bool stored, bool wide);
 size_t noalloc_scratch_bytes();
 hipError_t noalloc_scratch(void** p);
 hipError_t launch_inclusive_scan(int64_t* x, int64_t n, int64_t* tmp, hipStream_t s);
@@ -352,19 +352,24 @@ std::vector<std::tuple<int, int, int, int, int, double, int>> tune_key(const std
 }
 
 // Launch shapes of a handle that was not tuned.  The adjoint: 16 wavefronts on
-// a 16384-slot table, its slots added to the accumulators by atomics.  The
-// atomics overlap the walk of other tiles, while tile records (the other
-// flush) cost a reduction of 0.1-0.6 ms after it; the wide table merges more
-// of them per tile.  Measured (us per adjoint, 64 x 8 rows on the narrow
-// table with records -> the shape below): D = 59 59 -> 33, 952 147 -> 42,
-// 15,764 440 -> 108, 48,917 540 -> 259, 186,894 2040 -> 1143, 288,930 1497 ->
-// 1269, 581,740 2709 -> 2650.  Small bases give too few tiles of 64 rows to
-// fill the 256 CUs, so they are cut finer: at 15,764 rows 64-row tiles take
-// 132 us and 32-row tiles 108, at 48,917 rows 259 and 257.
+// an 8192-slot table, two such workgroups per CU, the slots added to the
+// accumulators by atomics.  The atomics overlap the walk of other tiles, while
+// tile records (the other flush) cost a reduction of 0.1-0.6 ms after it.  One
+// tile per workgroup, not a persistent grid: the device hands the next tile to
+// whichever CU is free (6Li Nmax = 6 1154 -> 1090 us).  Tiles of more rows
+// merge more of the atomics, but small bases then have too few of them for
+// 2 x 256 workgroups, and a table that overflows sends single terms to the
+// accumulators; 16 neutron determinants per tile pay only below 65,536 rows.
+// Measured (us per adjoint; 16384 slots and one workgroup per CU on 64 x 16
+// rows, 32 x 16 below 32,768 rows -> the shape below): D = 800 39 -> 31,
+// 15,764 106 -> 107, 36,779 224 -> 207, 48,917 255 -> 251, 139,816 967 -> 851,
+// 186,894 1147 -> 1090, 288,930 1261 -> 1089, 581,740 2772 -> 2153.  (96 rows
+// would take 2065 there, but the fixed-point grid coarsens with the rows.)
 ci_tuning default_tuning(int64_t nrows)
 {
-    const int adj_rows = nrows < 32768 ? 32 : 64;
-    return ci_tuning{4, 0, adj_rows, 16, 1, 96, 8, 1, 0, 1, 1};
+    const int adj_rows = nrows < 16384 ? 24 : nrows < 65536 ? 32 : 64;
+    const int adj_tile_n = nrows >= 16384 && nrows < 65536 ? 16 : 8;
+    return ci_tuning{4, 0, adj_rows, adj_tile_n, 0, 96, 8, 1, 0, 1, 1};
 }
 
 ci_tuning cached_tuning(const std::vector<ci_problem>& p, int64_t nrows)
@@ -1300,7 +1305,7 @@ static VjpLayout vjp_layout(const ci_basis* b, const ci_tuning& t, bool stored, 
     Layout L;
     (void)L.take<int64_t>((size_t)b->n_tbme);
     if (v.records) {
-        v.rec_cap = v.ntiles * (int64_t)adjoint_slots(stored || t.adj_wide);
+        v.rec_cap = v.ntiles * (int64_t)adjoint_slots(stored, t.adj_wide != 0);
         if (b->nnz_total >= 0) v.rec_cap = std::min<int64_t>(v.rec_cap, b->nnz_total / 2 + 1);
         v.rec_cap = std::min<int64_t>(v.rec_cap, INT32_MAX);  // record positions are int32 in the histograms
         v.hist = L.take<int32_t>((size_t)std::max<int64_t>(hist, 1));

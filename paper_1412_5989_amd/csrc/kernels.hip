@@ -30,6 +30,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "ci_internal.h"
 
@@ -111,13 +112,19 @@ __device__ __forceinline__ cptr<T> cst(const T* p)
 // proton determinant, and overlapping neutron moves), so the number of
 // device-scope atomics drops by that reuse factor.  A key that finds no slot
 // within kAdjProbes probes goes to the accumulator directly.
-// Two workgroup shapes: the adjoint that walks the partner lists has work to
-// overlap with its device-scope atomics and runs best at 8 wavefronts and a
-// 4096-slot table (three workgroups per CU); the adjoint that reads stored
-// words has little, and runs best with fewer atomics: 16 wavefronts sharing a
-// 16384-slot table (128 KiB of the CU's 160 KiB, one workgroup per CU).
+// Workgroup shapes.  The adjoint that walks the partner lists is bound by the
+// latency of its loads, so it wants every CU full (32 wavefronts): two
+// workgroups of 16 wavefronts on an 8192-slot table each (79 KiB of the CU's
+// 160), so that one walks while the other flushes; one workgroup on 16384 slots
+// took 2770 us on 10B Nmax = 4 where the two take 2153, and 1147
+// against 1090 on 6Li Nmax = 6.  Small tables (kAdjWaves) are the other choice
+// of the tuner.  The adjoint that reads stored words has little to overlap with
+// its device-scope atomics and runs best with fewer of them: 16 wavefronts
+// sharing a 16384-slot table (128 KiB, one workgroup per CU).
 constexpr int kAdjWaves = 8;
 constexpr int kAdjSlotBits = 12;
+constexpr int kAdjWideWaves = 16;
+constexpr int kAdjWideSlotBits = 13;
 constexpr int kAdjKeysWaves = 16;
 constexpr int kAdjKeysSlotBits = 14;
 constexpr int kAdjProbes = 16;
@@ -247,12 +254,14 @@ __device__ __forceinline__ bool rec_neg(uint64_t r) { return (r >> 56) & 1; }
 struct WaveLds {
     int32_t qpos[kQueue];  // offset from the row's first entry
     uint32_t qrec[kQueue]; // kind (0 diagonal, 1 one proton moved, 2 one neutron moved) | h << 8 | p << 16 | neg << 24
-    union {
-        int32_t toff[kQueue + 1];  // first term of each queued entry
-        double tsum[64];           // fill: one term per lane, summed by the entry's first lane
-    };
-    int32_t mark[64];  // load balancing: mark[x] = the lane whose item starts at x of the round
+    int8_t mark[64];   // load balancing: mark[x] = the lane whose item starts at x of the round
     uint8_t occ[128];  // occupied orbits of the row: protons, then neutrons
+};
+struct FillLds : WaveLds {
+    double tsum[64];  // one term per lane, summed by the entry's first lane
+};
+struct KeysLds : WaveLds {
+    int32_t toff[kQueue + 1];  // first term of each queued entry
 };
 
 // Load-balanced search: lanes hold consecutive non-overlapping ranges
@@ -273,10 +282,10 @@ __device__ __forceinline__ int owner_of(WaveLds& L, int start, int len, int x0, 
 {
     const int lane = threadIdx.x & 63;
     const int rel = start - x0;
-    if (len > 0 && rel >= 0 && rel < 64) L.mark[rel] = lane;
+    if (len > 0 && rel >= 0 && rel < 64) L.mark[rel] = (int8_t)lane;
     wave_sync();
     // owners are shifted by one so that "none" is 0, the identity of the maximum
-    const int o = wave_incl_max(max(L.mark[lane], *carry) + 1);
+    const int o = wave_incl_max(max((int)L.mark[lane], *carry) + 1);
     *carry = __builtin_amdgcn_readlane(o, 63) - 1;
     wave_sync();
     return o > 0 ? o - 1 : 0;
@@ -512,8 +521,8 @@ __device__ __forceinline__ int single_term(const RowView& R, const WaveLds& L, u
 // lanes' terms from LDS in order (FP64, rounded once).  Adjoint: every term
 // lane adds phase * G of its entry to the term's table position.  No search,
 // one path.
-template <int MODE>
-__device__ __forceinline__ void flush_singles(const RowView& R, WaveLds& L, int qn)
+template <int MODE, class Lds>
+__device__ __forceinline__ void flush_singles(const RowView& R, Lds& L, int qn)
 {
     const int lane = threadIdx.x & 63;
     const int nt = R.Z + R.NN - 1 + R.B->kinetic;
@@ -549,22 +558,23 @@ __device__ __forceinline__ void flush_singles(const RowView& R, WaveLds& L, int 
                 }
             }
         }
-        if (MODE == kAdjoint) continue;
-        L.tsum[lane] = v;
-        wave_sync();
-        if (act && lane == k * nt) {
-            double sum = 0.0;
-            for (int i = 0; i < nt && i < 64; i++) sum += L.tsum[lane + i];
-            const int64_t p = R.pos0 + L.qpos[q];
-            if (p < R.cap) glbw(R.val)[p] = (float)sum;
+        if constexpr (MODE == kFill) {
+            L.tsum[lane] = v;
+            wave_sync();
+            if (act && lane == k * nt) {
+                double sum = 0.0;
+                for (int i = 0; i < nt && i < 64; i++) sum += L.tsum[lane + i];
+                const int64_t p = R.pos0 + L.qpos[q];
+                if (p < R.cap) glbw(R.val)[p] = (float)sum;
+            }
+            wave_sync();
         }
-        wave_sync();
     }
 }
 
 // Scatter the queued multi-term entries (diagonal or one nucleon moved) of the
 // adjoint that reads stored words.
-__device__ void flush_queue(const RowView& R, WaveLds& L, int qn)
+__device__ void flush_queue(const RowView& R, KeysLds& L, int qn)
 {
     const int lane = threadIdx.x & 63;
     if (qn == 0) return;
@@ -658,8 +668,8 @@ __device__ void row_occ(const BasisDev& B, WaveLds& L, RowView& R, int gP, int g
 }
 
 // One row: fill or adjoint.
-template <int MODE>
-__device__ void do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView& R)
+template <int MODE, class Lds>
+__device__ void do_row(const BasisDev& B, Lds& L, int bi, int r, RowView& R)
 {
     const int lane = threadIdx.x & 63;
     const SpeciesDev& SP = B.sp[0];
@@ -847,7 +857,7 @@ __device__ void do_row(const BasisDev& B, WaveLds& L, int bi, int r, RowView& R)
 // entries [R.pos0, end) are read in order, single terms go straight to the
 // accumulators and multi-term entries through the queue; the partner lists
 // are not walked.
-__device__ void do_row_keys(const BasisDev& B, WaveLds& L, int bi, int r, RowView& R, int64_t end)
+__device__ void do_row_keys(const BasisDev& B, KeysLds& L, int bi, int r, RowView& R, int64_t end)
 {
     const int lane = threadIdx.x & 63;
     const int kp = uniform(cst(B.blk_kp)[bi]), kn = uniform(cst(B.blk_kn)[bi]);
@@ -907,13 +917,13 @@ __device__ __forceinline__ int block_of(const int64_t* off, int nblocks, int64_t
 }
 
 // Row i of basis B, row r of its block bi.
-template <int MODE, bool KEYS>
+template <int MODE, bool KEYS, class Lds>
 __device__ __forceinline__ void run_row_at(const BasisDev& B, int bi, int i, int r, const float* __restrict__ tbme,
                                            const int64_t* __restrict__ row_ptr, int64_t nrp, int32_t* __restrict__ col,
                                            float* __restrict__ val, const float* __restrict__ gval,
                                            unsigned long long* __restrict__ gacc, lptr<uint32_t> hkey,
                                            lptr<int32_t> hval, bool use_table, int hbits, int qshift, bool full,
-                                           uint32_t* keys, WaveLds& L)
+                                           uint32_t* keys, Lds& L)
 {
     RowView R;
     R.B = &B;
@@ -947,7 +957,7 @@ __device__ __forceinline__ void fill_row(const BasisDev* __restrict__ bases, con
                                          const int32_t* __restrict__ blk_local, int nblocks,
                                          const int64_t* __restrict__ row_off, int64_t g, const float* __restrict__ tbme,
                                          const int64_t* __restrict__ row_ptr, int64_t nrp, int32_t* __restrict__ col,
-                                         float* __restrict__ val, bool full, uint32_t* keys, WaveLds& L)
+                                         float* __restrict__ val, bool full, uint32_t* keys, FillLds& L)
 {
     const int gb = block_of(row_off, nblocks, g);
     const BasisDev& B = bases[uniform(cst(blk_basis)[gb])];
@@ -970,7 +980,7 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
                int32_t* __restrict__ col, float* __restrict__ val, uint32_t* __restrict__ keys, int grab,
                unsigned long long* __restrict__ queue, int full, int xcd)
 {
-    __shared__ WaveLds lds[WAVES];
+    __shared__ FillLds lds[WAVES];
     const int wid = uniform(threadIdx.x >> 6);
     const int64_t nrows = uniform64(cst(row_off)[nblocks]);
     for (;;) {
@@ -1200,7 +1210,7 @@ __global__ void __launch_bounds__(256) tile_offsets(const BasisDev* __restrict__
 // gacc and no record is written.
 // KEYS: from the words the fill stored, else by walking the partner lists.
 template <int WAVES, int SLOT_BITS, bool KEYS>
-__global__ void __launch_bounds__(64 * WAVES)
+__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(8, 8)))
     adjoint_kernel(const BasisDev* __restrict__ bases, const int32_t* __restrict__ blk_basis,
                    const int32_t* __restrict__ blk_local, int nblocks, const int64_t* __restrict__ tile_off,
                    int rows, int tile_n, const int64_t* __restrict__ row_ptr, int64_t nrp,
@@ -1212,10 +1222,14 @@ __global__ void __launch_bounds__(64 * WAVES)
 {
     constexpr int kSlots = 1 << SLOT_BITS;
     constexpr int kThreads = 64 * WAVES;
-    __shared__ WaveLds lds[WAVES];
+    __shared__ union {  // the rows and the flush take turns
+        typename std::conditional<KEYS, KeysLds, WaveLds>::type lds[WAVES];
+        int32_t bcur[kAdjMaxBuckets + 1];  // bucket counts, then cursors
+    } sh;
     __shared__ uint32_t hkey[kSlots];
     __shared__ int32_t hval[kSlots];  // fixed-point tile sums
-    __shared__ int32_t bcur[kAdjMaxBuckets + 1];  // bucket counts, then cursors
+    auto& lds = sh.lds;
+    int32_t* bcur = sh.bcur;
     __shared__ int next_row;
     __shared__ int t_gb, t_ip0, t_in0, t_tp, t_tn, t_nKn, t_valid;
     __shared__ int64_t t_g, t_base;
@@ -1227,36 +1241,46 @@ __global__ void __launch_bounds__(64 * WAVES)
     const int lane = threadIdx.x & 63;
     const int64_t ntiles = tile_off[nblocks];
     for (;;) {
-        if (threadIdx.x == 0) {
-            next_row = 0;
-            const int64_t g = persistent ? (int64_t)__hip_atomic_fetch_add(glbw(queue), 1ull, __ATOMIC_RELAXED,
-                                                                            __HIP_MEMORY_SCOPE_AGENT)
-                                         : (xcd ? xcd_contiguous(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x);
-            t_valid = g < ntiles;
-            t_g = g;
-            if (g < ntiles) {
-                // block of the tile: largest gb with tile_off[gb] <= g
-                int lo = 0, hi = nblocks;
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (tile_off[mid] <= g) lo = mid;
-                    else hi = mid;
+        if (wid == 0) {
+            int64_t g = xcd ? xcd_contiguous(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+            if (persistent) {
+                unsigned long long t = 0;
+                if (lane == 0)
+                    t = __hip_atomic_fetch_add(glbw(queue), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                g = uniform64((int64_t)t);
+            }
+            // block of the tile: largest gb with tile_off[gb] <= g, in
+            // [lo, lo + n); every step splits the range in 64 (the other 15
+            // wavefronts wait for this chain of loads)
+            int lo = 0, n = nblocks;
+            while (n > 1) {
+                const int step = (n + 63) / 64, at = lo + lane * step;
+                const bool le = lane * step < n && glb(tile_off)[at] <= g;
+                const int c = max(__popcll(__ballot(le)) - 1, 0);
+                lo += c * step;
+                n = min(step, n - c * step);
+            }
+            if (lane == 0) {
+                next_row = 0;
+                t_valid = g < ntiles;
+                t_g = g;
+                if (g < ntiles) {
+                    const BasisDev& B = bases[blk_basis[lo]];
+                    const int bi = blk_local[lo];
+                    const int kn = B.blk_kn[bi];
+                    const int nKn = B.sp[1].key_off[kn + 1] - B.sp[1].key_off[kn];
+                    const int nKp = (int)((B.blk_off[bi + 1] - B.blk_off[bi]) / nKn);
+                    int tp, tn;
+                    block_tile_shape(nKp, nKn, rows, tile_n, &tp, &tn);
+                    const int t = (int)(g - tile_off[lo]), ntn = (nKn + tn - 1) / tn;
+                    const int ip0 = (t / ntn) * tp, in0 = (t % ntn) * tn;
+                    t_gb = lo;
+                    t_ip0 = ip0;
+                    t_in0 = in0;
+                    t_tp = (nKp - ip0) < tp ? nKp - ip0 : tp;
+                    t_tn = (nKn - in0) < tn ? nKn - in0 : tn;
+                    t_nKn = nKn;
                 }
-                const BasisDev& B = bases[blk_basis[lo]];
-                const int bi = blk_local[lo];
-                const int kn = B.blk_kn[bi];
-                const int nKn = B.sp[1].key_off[kn + 1] - B.sp[1].key_off[kn];
-                const int nKp = (int)((B.blk_off[bi + 1] - B.blk_off[bi]) / nKn);
-                int tp, tn;
-                block_tile_shape(nKp, nKn, rows, tile_n, &tp, &tn);
-                const int t = (int)(g - tile_off[lo]), ntn = (nKn + tn - 1) / tn;
-                const int ip0 = (t / ntn) * tp, in0 = (t % ntn) * tn;
-                t_gb = lo;
-                t_ip0 = ip0;
-                t_in0 = in0;
-                t_tp = (nKp - ip0) < tp ? nKp - ip0 : tp;
-                t_tn = (nKn - in0) < tn ? nKn - in0 : tn;
-                t_nKn = nKn;
             }
         }
         __syncthreads();
@@ -1759,11 +1783,11 @@ hipError_t launch_vjp(const BasisDev* bases, int nbases, const int32_t* blk_basi
     if (walked) {
         hipLaunchKernelGGL(tile_offsets, dim3(1), dim3(256), 0, s, bases, blk_basis, blk_local, nblocks, rows, tile_n,
                            tile_off, nbases, adjb);
-        const bool wide = keys || t.adj_wide;  // 16 wavefronts, 16384-slot table
+        const bool wide = keys || t.adj_wide;  // 16 wavefronts
         const auto kern = keys   ? adjoint_kernel<kAdjKeysWaves, kAdjKeysSlotBits, true>
-                          : wide ? adjoint_kernel<kAdjKeysWaves, kAdjKeysSlotBits, false>
+                          : wide ? adjoint_kernel<kAdjWideWaves, kAdjWideSlotBits, false>
                                  : adjoint_kernel<kAdjWaves, kAdjSlotBits, false>;
-        const int threads = 64 * (wide ? kAdjKeysWaves : kAdjWaves);
+        const int threads = 64 * (keys ? kAdjKeysWaves : wide ? kAdjWideWaves : kAdjWaves);
         unsigned grid = (unsigned)ntiles;
         if (recs) hipLaunchKernelGGL(zero_u64, dim3(1), dim3(1), 0, s, rec_count);
         if (t.adj_persistent) {
@@ -1790,6 +1814,9 @@ hipError_t launch_vjp(const BasisDev* bases, int nbases, const int32_t* blk_basi
 }
 
 // Slots of the shared-memory table of each adjoint (the records a tile can write).
-int adjoint_slots(bool wide) { return wide ? (1 << kAdjKeysSlotBits) : (1 << kAdjSlotBits); }
+int adjoint_slots(bool stored, bool wide)
+{
+    return 1 << (stored ? kAdjKeysSlotBits : wide ? kAdjWideSlotBits : kAdjSlotBits);
+}
 
 }  // namespace ci
