@@ -365,11 +365,18 @@ std::vector<std::tuple<int, int, int, int, int, double, int>> tune_key(const std
 // 15,764 106 -> 107, 36,779 224 -> 207, 48,917 255 -> 251, 139,816 967 -> 851,
 // 186,894 1147 -> 1090, 288,930 1261 -> 1089, 581,740 2772 -> 2153.  (96 rows
 // would take 2065 there, but the fixed-point grid coarsens with the rows.)
+// The adjoint from stored words keeps 16384 slots and one workgroup per CU
+// (8192 and two: 899 -> 1062 us at D = 186,894; it is bound by the atomics).
+// Measured (us; 96 x 8 rows, persistent -> the shape below): D = 15,764 114 ->
+// 91, 48,917 233 -> 194, 186,894 903 (96 x 8), 288,930 934 -> 875, 581,740
+// 1708 -> 1582.
 ci_tuning default_tuning(int64_t nrows)
 {
     const int adj_rows = nrows < 16384 ? 24 : nrows < 65536 ? 32 : 64;
     const int adj_tile_n = nrows >= 16384 && nrows < 65536 ? 16 : 8;
-    return ci_tuning{4, 0, adj_rows, adj_tile_n, 0, 96, 8, 1, 0, 1, 1};
+    const bool small = nrows < 65536, large = nrows >= 250000;
+    const int adjk_rows = small ? 64 : large ? 128 : 96, adjk_tile_n = small || large ? 16 : 8;
+    return ci_tuning{4, 0, adj_rows, adj_tile_n, 0, adjk_rows, adjk_tile_n, small ? 0 : 1, 0, 1, 1};
 }
 
 ci_tuning cached_tuning(const std::vector<ci_problem>& p, int64_t nrows)
