@@ -38,16 +38,12 @@ namespace ci {
 
 enum { kFill = 1, kAdjoint = 2 };
 
-constexpr int kWavesPerBlock = 4;
 constexpr int kQueue = 96;  // queued multi-term entries per wave
 
 __device__ __forceinline__ int rec_d(uint64_t r) { return (int)((r >> 57) & 3); }
 __device__ __forceinline__ int rec_local(uint64_t r) { return (int)(r & kRecLocalMask); }
 __device__ __forceinline__ int rec_h1(uint64_t r) { return (int)((r >> 24) & 255); }
 __device__ __forceinline__ int rec_p1(uint64_t r) { return (int)((r >> 32) & 255); }
-__device__ __forceinline__ int rec_h2(uint64_t r) { return (int)((r >> 40) & 255); }
-__device__ __forceinline__ int rec_p2(uint64_t r) { return (int)((r >> 48) & 255); }
-__device__ __forceinline__ double rec_sign(uint64_t r) { return ((r >> 56) & 1) ? -1.0 : 1.0; }
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -193,16 +189,6 @@ __device__ __forceinline__ double wave_sum_f64(double v)
     return v;
 }
 
-// largest t in [0, 64) with a[t] <= x, for a[0] <= x < a[64], a non-decreasing
-__device__ __forceinline__ int seg_search64(const int32_t* a, int x)
-{
-    int lo = 0;
-#pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-        if (a[lo + step] <= x) lo += step;
-    return lo;
-}
-
 // largest t in [0, n) with a[t] <= x, for a[0] <= x < a[n], a non-decreasing
 __device__ __forceinline__ int seg_search(const int32_t* a, int n, int x)
 {
@@ -247,7 +233,6 @@ __device__ __forceinline__ int tb_pos_any(const BasisDev& B, int cls, int a, int
 
 __device__ __forceinline__ bool rec_neg(uint64_t r) { return (r >> 56) & 1; }
 
-// Per-wavefront LDS.
 // Per-wavefront LDS: the queue of multi-term entries and the row's occupied
 // orbits.  The per-block and per-segment values of the walk stay in registers
 // (lane t holds block / segment t) and are read across lanes with ds_bpermute.
@@ -303,17 +288,6 @@ __device__ __forceinline__ uint64_t lane_read64(uint64_t v, int l)
     const uint32_t lo = (uint32_t)lane_read((int)(uint32_t)v, l);
     const uint32_t hi = (uint32_t)lane_read((int)(uint32_t)(v >> 32), l);
     return ((uint64_t)hi << 32) | lo;
-}
-
-// largest t in [0, 64) with start(t) <= x, where lane t holds start(t),
-// non-decreasing in t, and start(0) <= x (every lane active)
-__device__ __forceinline__ int lane_search64(int start, int x)
-{
-    int lo = 0;
-#pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-        if (lane_read(start, lo + step) <= x) lo += step;
-    return lo;
 }
 
 // Word stored per entry for the adjoint: a single two-body term holds its
