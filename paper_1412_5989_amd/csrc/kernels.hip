@@ -495,6 +495,12 @@ __device__ __forceinline__ int single_term(const RowView& R, const WaveLds& L, u
 // lanes' terms from LDS in order (FP64, rounded once).  Adjoint: every term
 // lane adds phase * G of its entry to the term's table position.  No search,
 // one path.
+// The fill of nt > 32, where a round would hold one entry and its one summing
+// lane would read up to 64 terms after each other: four entries at a time,
+// first their terms past 64 together (16 lanes each: nt <= 80), then entry by
+// entry, the lanes' terms summed by the wavefront.  Fill of Z = N = 40, Nmax =
+// 2 (51,301 rows, nt = 79) 2280 -> 1670 us, Z = N = 20, Nmax = 2 (10,257 rows,
+// nt = 39) 469 -> 295; no difference below nt = 33.
 template <int MODE, class Lds>
 __device__ __forceinline__ void flush_singles(const RowView& R, Lds& L, int qn)
 {
@@ -506,6 +512,32 @@ __device__ __forceinline__ void flush_singles(const RowView& R, Lds& L, int qn)
                 const int64_t p = R.pos0 + L.qpos[q];
                 if (p < R.cap) glbw(R.val)[p] = 0.0f;
             }
+        wave_sync();
+        return;
+    }
+    if (MODE == kFill && nt > 32) {
+        const int mine = lane >> 4;
+        for (int q0 = 0; q0 < qn; q0 += 4) {
+            double rest = 0.0;  // the lane's term past 64, of entry q0 + mine
+            for (int k = -1; k < 4 && q0 + k < qn; k++) {
+                const int q = q0 + (k < 0 ? mine : k), u = k < 0 ? 64 + (lane & 15) : lane;
+                double v = 0.0;
+                if (q < qn && u < nt) {
+                    bool neg;
+                    double ob;
+                    const int kk = single_term(R, L, L.qrec[q], u, &neg, &ob);
+                    const double x = kk >= 0 ? (double)glb(R.tbme)[kk] : ob;
+                    v = neg ? -x : x;
+                }
+                if (k < 0) {
+                    rest = v;
+                } else {
+                    const double sum = wave_sum_f64(mine == k ? v + rest : v);
+                    const int64_t p = R.pos0 + L.qpos[q];
+                    if (lane == 0 && p < R.cap) glbw(R.val)[p] = (float)sum;
+                }
+            }
+        }
         wave_sync();
         return;
     }
@@ -537,7 +569,7 @@ __device__ __forceinline__ void flush_singles(const RowView& R, Lds& L, int qn)
             wave_sync();
             if (act && lane == k * nt) {
                 double sum = 0.0;
-                for (int i = 0; i < nt && i < 64; i++) sum += L.tsum[lane + i];
+                for (int i = 0; i < nt; i++) sum += L.tsum[lane + i];
                 const int64_t p = R.pos0 + L.qpos[q];
                 if (p < R.cap) glbw(R.val)[p] = (float)sum;
             }
@@ -583,7 +615,11 @@ __device__ void flush_queue(const RowView& R, KeysLds& L, int qn)
 // occupied pair V_{ab,ab}, one lane per pair, summed in FP64 in a fixed order
 // and rounded once; adjoint, G of the entry added to every occupied pair's
 // table position.  Lane u takes pair u of the A nucleons (protons, then
-// neutrons) in colex order (u = y(y-1)/2 + x, x < y).
+// neutrons) in colex order (u = y(y-1)/2 + x, x < y).  The fill counts the
+// nucleons from the last one, so that neighbouring lanes share a and read
+// neighbouring words of the pair table (fill of Z = 39, N = 38, Nmax = 1,
+// 166,688 rows of 2926 pairs: 3310 -> 2590 us; counted from the first one
+// instead, neighbours share b).  The adjoint is 2 % faster the other way round.
 template <int MODE>
 __device__ void row_diagonal(const RowView& R, const WaveLds& L, int64_t p)
 {
@@ -600,7 +636,8 @@ __device__ void row_diagonal(const RowView& R, const WaveLds& L, int64_t p)
             if (y * (y - 1) / 2 > u) y--;  // u < 2^12: the root is off by one rounding at most
             else if ((y + 1) * y / 2 <= u) y++;
             const int x = u - y * (y - 1) / 2;
-            const int k = tb_pos(B, y < Z ? 0 : (x < Z ? 1 : 2), L.occ[x], L.occ[y], L.occ[x], L.occ[y]);
+            const int i = MODE == kFill ? Z + NN - 1 - y : x, j = MODE == kFill ? Z + NN - 1 - x : y;
+            const int k = tb_pos(B, j < Z ? 0 : (i < Z ? 1 : 2), L.occ[i], L.occ[j], L.occ[i], L.occ[j]);
             if (MODE == kFill) acc += (double)glb(R.tbme)[k];
             if (MODE == kAdjoint && p < R.cap) adj_add(R, k, g);
         }

@@ -1,0 +1,51 @@
+"""Times of one pass against another on the same GPU (gpu): paths that were
+once slower than what they replaced.  Each time is the smallest of many, the
+two taken in turn, and the bound lies well between the two ratios measured."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ci():
+    import paper_1412_5989_amd as m
+
+    return m
+
+
+def ratio(f, g, reps=12):
+    """Smallest time of f over smallest time of g."""
+    a, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = [float("inf"), float("inf")]
+    for _ in range(reps):
+        for k, h in enumerate((f, g)):
+            a.record()
+            h()
+            e.record()
+            e.synchronize()
+            best[k] = min(best[k], a.elapsed_time(e))
+    print("times (us)", [round(1e3 * t, 1) for t in best], flush=True)
+    return best[0] / best[1]
+
+
+def problem(ci, p):
+    """Basis, row_ptr, two-body table, upstream gradient."""
+    b = ci.ci_basis_build([p])
+    rp, nnz = ci.ci_hamiltonian_count(b)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    t = torch.randn(b.n_tbme, device="cuda", generator=gen)
+    G = torch.randn(sum(nnz), device="cuda", generator=gen)
+    return b, rp, t, G
+
+
+# 80 nucleons: sums of 79 terms and of 3160 pairs (8.2 times the fill of 8Be
+# with twice the entries when one lane summed them and neighbouring lanes read
+# far-apart words, 5.4 now)
+def test_fill_of_many_nucleons(ci):
+    f = []
+    for p in ((40, 40, 2, 0, 1), (4, 4, 4, 0, 1)):
+        b, rp, t, G = problem(ci, p)
+        col, val = ci.ci_hamiltonian_fill(b, t, rp)
+        f.append(lambda b=b, rp=rp, t=t, col=col, val=val: ci.ci_hamiltonian_fill(b, t, rp, col, val))
+    assert ratio(*f) < 6.8
