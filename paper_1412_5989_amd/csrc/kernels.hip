@@ -1091,15 +1091,15 @@ __device__ __forceinline__ GroupBlock group_block(const BasisDev& B, const Group
 }
 
 // group_off[gb] (global block list) is the number of groups of the blocks
-// before gb; ngroups their total.
+// before gb; the launch takes groups [g0, g1).
 __global__ void __launch_bounds__(256)
     count_kernel(const BasisDev* __restrict__ bases, const int32_t* __restrict__ blk_basis,
                  const int32_t* __restrict__ blk_local, int nblocks, const int64_t* __restrict__ group_off,
-                 int64_t ngroups, int64_t* __restrict__ row_ptr, int full)
+                 int64_t g0, int64_t g1, int64_t* __restrict__ row_ptr, int full)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t u = (int64_t)blockIdx.x * 4 + uniform(threadIdx.x >> 6);
-    if (u >= ngroups) return;
+    const int64_t u = g0 + (int64_t)blockIdx.x * 4 + uniform(threadIdx.x >> 6);
+    if (u >= g1) return;
     const int gb = block_of(group_off, nblocks, u);
     const BasisDev& B = bases[uniform(cst(blk_basis)[gb])];
     const int bi = uniform(cst(blk_local)[gb]);
@@ -1673,6 +1673,11 @@ __global__ void nnz_of_bases(const int64_t* __restrict__ row_ptr, const int64_t*
 
 static inline unsigned grid_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
+// A launch of 2^32 threads or more runs, without an error, only what is left
+// modulo 2^32.  Grids that grow with the rows of a handle (one wavefront per
+// row or group, one workgroup per adjoint tile) are cut or made persistent here.
+constexpr int64_t kMaxLaunchThreads = 0xffffffffLL;
+
 hipError_t launch_inclusive_scan(int64_t* x, int64_t n, int64_t* tmp, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
@@ -1717,9 +1722,12 @@ static unsigned resident_blocks(const void* kernel, int threads, int kind)
 hipError_t launch_count(const BasisDev* bases, int nb, const RowWork& w, int64_t* row_ptr, int64_t nrp,
                         const int64_t* seg_first, int64_t* scan_tmp, int full, hipStream_t s)
 {
-    if (w.ngroups > 0)
-        hipLaunchKernelGGL(count_kernel, dim3(grid_for(w.ngroups, 4)), dim3(256), 0, s, bases, w.blk_basis,
-                           w.blk_local, w.nblocks, w.group_off, w.ngroups, row_ptr, full);
+    constexpr int64_t kMost = kMaxLaunchThreads / 256 * 4;  // groups of one launch
+    for (int64_t g0 = 0; g0 < w.ngroups; g0 += kMost) {
+        const int64_t g1 = w.ngroups - g0 < kMost ? w.ngroups : g0 + kMost;
+        hipLaunchKernelGGL(count_kernel, dim3(grid_for(g1 - g0, 4)), dim3(256), 0, s, bases, w.blk_basis,
+                           w.blk_local, w.nblocks, w.group_off, g0, g1, row_ptr, full);
+    }
     // the first slot of each basis' segment holds 0 before the scan, so the
     // inclusive scan leaves there the number of entries of the bases before it
     hipLaunchKernelGGL(zero_i64_at, dim3(grid_for(nb, 256)), dim3(256), 0, s, row_ptr, seg_first, nb);
@@ -1738,6 +1746,7 @@ static void launch_fill_w(const BasisDev* bases, const RowWork& w, const float* 
                           int64_t nrp, int32_t* col, float* val, uint32_t* keys, int grab, unsigned long long* queue,
                           int full, int xcd, hipStream_t s)
 {
+    if (grab <= 0 && w.nrows > kMaxLaunchThreads / (64 * WAVES) * WAVES) grab = 16;
     unsigned grid = grid_for(w.nrows, WAVES);
     if (grab > 0) {
         hipLaunchKernelGGL(zero_u64, dim3(1), dim3(1), 0, s, queue);
@@ -1799,15 +1808,15 @@ hipError_t launch_vjp(const BasisDev* bases, int nbases, const int32_t* blk_basi
                           : wide ? adjoint_kernel<kAdjWideWaves, kAdjWideSlotBits, false>
                                  : adjoint_kernel<kAdjWaves, kAdjSlotBits, false>;
         const int threads = 64 * (keys ? kAdjKeysWaves : wide ? kAdjWideWaves : kAdjWaves);
-        unsigned grid = (unsigned)ntiles;
+        int64_t grid = ntiles;
         if (recs) hipLaunchKernelGGL(zero_u64, dim3(1), dim3(1), 0, s, rec_count);
-        if (t.adj_persistent) {
+        const bool persistent = t.adj_persistent || ntiles > kMaxLaunchThreads / threads;
+        if (persistent) {
             hipLaunchKernelGGL(zero_u64, dim3(1), dim3(1), 0, s, queue);
-            const unsigned res = resident_blocks((const void*)kern, threads, keys ? 7 : (wide ? 8 : 6));
-            grid = res < grid ? res : grid;
+            grid = std::min<int64_t>(grid, resident_blocks((const void*)kern, threads, keys ? 7 : (wide ? 8 : 6)));
         }
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, s, bases, blk_basis, blk_local, nblocks, tile_off, rows,
-                           tile_n, row_ptr, nrp, gval, keys, gacc, use_table, t.adj_persistent ? 1 : 0, queue, adjb,
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, s, bases, blk_basis, blk_local, nblocks, tile_off, rows,
+                           tile_n, row_ptr, nrp, gval, keys, gacc, use_table, persistent ? 1 : 0, queue, adjb,
                            recs, rec_cap, rec_count, hist, gscale, t.row_xcd);
     }
     if (ntbme > 0) {
