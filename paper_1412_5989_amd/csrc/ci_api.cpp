@@ -351,6 +351,22 @@ std::vector<std::tuple<int, int, int, int, int, double, int>> tune_key(const std
     return k;
 }
 
+// Adjoint tiles of one basis (block_tile_shape of kernels.hip, per block).
+int64_t count_tiles_of(const HostBasis& hb, const ci_tuning& t, bool stored)
+{
+    const int64_t rows = stored ? t.adjk_rows : t.adj_rows, tile_n = stored ? t.adjk_tile_n : t.adj_tile_n;
+    int64_t n = 0;
+    for (int bi = 0; bi < hb.nblk(); bi++) {
+        const HostSpecies &P = hb.sp[0], &N = hb.sp[1];
+        const int64_t nKp = P.key_off[hb.blk_kp[bi] + 1] - P.key_off[hb.blk_kp[bi]];
+        const int64_t nKn = N.key_off[hb.blk_kn[bi] + 1] - N.key_off[hb.blk_kn[bi]];
+        const int64_t tn = std::min<int64_t>(tile_n, nKn);
+        const int64_t tp = std::max<int64_t>(1, rows / tn);
+        n += ((nKp + tp - 1) / tp) * ((nKn + tn - 1) / tn);
+    }
+    return n;
+}
+
 // Launch shapes of a handle that was not tuned.  The adjoint: 16 wavefronts on
 // an 8192-slot table, two such workgroups per CU, the slots added to the
 // accumulators by atomics.  The atomics overlap the walk of other tiles, while
@@ -370,20 +386,37 @@ std::vector<std::tuple<int, int, int, int, int, double, int>> tune_key(const std
 // Measured (us; 96 x 8 rows, persistent -> the shape below): D = 15,764 114 ->
 // 91, 48,917 233 -> 194, 186,894 903 (96 x 8), 288,930 934 -> 875, 581,740
 // 1708 -> 1582.
-ci_tuning default_tuning(int64_t nrows)
+// From 65,536 rows on, a basis whose blocks hold few proton determinants leaves
+// 64 x 8 tiles mostly empty: below 32 rows per tile on average the neutron
+// width is 32, on a persistent grid (the same 64 rows, so the same fixed-point
+// grid).  Measured (us per adjoint; 64 x 8 -> 64 x 32; Z, N, Nmax and rows per
+// 64 x 8 tile): 0, 10, 4 (8.0) 773 -> 457; 0, 7, 6 (8.0) 849 -> 551; 1, 9, 4
+// (9.6) 740 -> 555; 2, 5, 6 (25.6) 592 -> 491; 2, 4, 6 (31.4) 973 -> 882; 3, 3, 6
+// (47.8) 1110 -> 1261; 4, 4, 4 (49.7) 638 -> 698.
+ci_tuning default_tuning(const std::vector<std::shared_ptr<HostBasis>>& host, int64_t nrows)
 {
     const int adj_rows = nrows < 16384 ? 24 : nrows < 65536 ? 32 : 64;
     const int adj_tile_n = nrows >= 16384 && nrows < 65536 ? 16 : 8;
     const bool small = nrows < 65536, large = nrows >= 250000;
     const int adjk_rows = small ? 64 : large ? 128 : 96, adjk_tile_n = small || large ? 16 : 8;
-    return ci_tuning{4, 0, adj_rows, adj_tile_n, 0, adjk_rows, adjk_tile_n, small ? 0 : 1, 0, 1, 1};
+    ci_tuning t{4, 0, adj_rows, adj_tile_n, 0, adjk_rows, adjk_tile_n, small ? 0 : 1, 0, 1, 1};
+    if (!small) {
+        int64_t tiles = 0;
+        for (const auto& hb : host) tiles += count_tiles_of(*hb, t, false);
+        if (nrows < 32 * tiles) {
+            t.adj_tile_n = 32;
+            t.adj_persistent = 1;
+        }
+    }
+    return t;
 }
 
-ci_tuning cached_tuning(const std::vector<ci_problem>& p, int64_t nrows)
+ci_tuning cached_tuning(const std::vector<ci_problem>& p, const std::vector<std::shared_ptr<HostBasis>>& host,
+                        int64_t nrows)
 {
     std::lock_guard<std::mutex> g(g_tune_mu);
     auto it = g_tune.find(tune_key(p));
-    return it == g_tune.end() ? default_tuning(nrows) : it->second;
+    return it == g_tune.end() ? default_tuning(host, nrows) : it->second;
 }
 
 void remember_tuning(const std::vector<ci_problem>& p, const ci_tuning& t)
@@ -924,7 +957,7 @@ int ci_basis_build(const ci_problem* probs, int32_t n_probs, ci_basis_info* info
     h->d_adjb = (AdjBasis*)D(P->o_adjb);
     h->nblocks = P->nblocks;
     h->probs.assign(probs, probs + n_probs);
-    h->tune = cached_tuning(h->probs, h->nrows);
+    h->tune = cached_tuning(h->probs, h->host, h->nrows);
     h->n_rowptr = R;
     h->n_tbme = T;
     // the partner lists are still being counted on the stream
@@ -1252,21 +1285,6 @@ int ci_hamiltonian3_fill_full(ci_basis* b, const float* tbme, const ci_v3* v3, c
 
 // Adjoint tiles of basis p for shape t (the device computes the same counts
 // in tile_offsets).
-static int64_t count_tiles_of(const HostBasis& hb, const ci_tuning& t, bool stored)
-{
-    const int64_t rows = stored ? t.adjk_rows : t.adj_rows, tile_n = stored ? t.adjk_tile_n : t.adj_tile_n;
-    int64_t n = 0;
-    for (int bi = 0; bi < hb.nblk(); bi++) {
-        const HostSpecies &P = hb.sp[0], &N = hb.sp[1];
-        const int64_t nKp = P.key_off[hb.blk_kp[bi] + 1] - P.key_off[hb.blk_kp[bi]];
-        const int64_t nKn = N.key_off[hb.blk_kn[bi] + 1] - N.key_off[hb.blk_kn[bi]];
-        const int64_t tn = std::min<int64_t>(tile_n, nKn);
-        const int64_t tp = std::max<int64_t>(1, rows / tn);
-        n += ((nKp + tp - 1) / tp) * ((nKn + tn - 1) / tn);
-    }
-    return n;
-}
-
 // Work buffer of one adjoint launch: int64 fixed-point accumulators of the
 // contributions that find no table slot (or no room in the record buffer)
 // [n_tbme], the tile records (uint64: table position | int32 fixed-point tile
