@@ -345,7 +345,8 @@ size_t ci_vjp_work_bytes(const ci_basis* b);
 
 /* Autotuner (batched construction): times every candidate launch shape of
  * the fill and of both adjoints on the caller's buffers (one warm-up and
- * `reps` timed runs each, with HIP events on `stream`), keeps the fastest in
+ * `reps` timed runs each, with HIP events on `stream`; from 512 rows on the
+ * shapes that the handle has and the untuned ones are among them), keeps the fastest in
  * the handle, and remembers it for handles later built from the same problem
  * list in this process.  keys (device uint32 [nnz], may be NULL): room for the
  * stored words; with it the fill writes them once and the shapes of the

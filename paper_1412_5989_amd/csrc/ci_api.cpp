@@ -411,12 +411,11 @@ ci_tuning default_tuning(const std::vector<std::shared_ptr<HostBasis>>& host, in
     return t;
 }
 
-ci_tuning cached_tuning(const std::vector<ci_problem>& p, const std::vector<std::shared_ptr<HostBasis>>& host,
-                        int64_t nrows)
+ci_tuning cached_tuning(const std::vector<ci_problem>& p, const ci_tuning& untuned)
 {
     std::lock_guard<std::mutex> g(g_tune_mu);
     auto it = g_tune.find(tune_key(p));
-    return it == g_tune.end() ? default_tuning(host, nrows) : it->second;
+    return it == g_tune.end() ? untuned : it->second;
 }
 
 void remember_tuning(const std::vector<ci_problem>& p, const ci_tuning& t)
@@ -463,6 +462,7 @@ struct ci_basis {
     mutable int64_t nnz_total = -1;         // stored entries of all bases (after the upper-triangle count)
     int nblocks = 0;
     ci_tuning tune{};
+    ci_tuning untuned{};                    // what tune is without a tuner's choice
     std::vector<ci_problem> probs;          // key of the process-wide tuning cache
     int64_t n_rowptr = 0;
     int64_t n_tbme = 0;
@@ -957,7 +957,8 @@ int ci_basis_build(const ci_problem* probs, int32_t n_probs, ci_basis_info* info
     h->d_adjb = (AdjBasis*)D(P->o_adjb);
     h->nblocks = P->nblocks;
     h->probs.assign(probs, probs + n_probs);
-    h->tune = cached_tuning(h->probs, h->host, h->nrows);
+    h->untuned = default_tuning(h->host, h->nrows);
+    h->tune = cached_tuning(h->probs, h->untuned);
     h->n_rowptr = R;
     h->n_tbme = T;
     // the partner lists are still being counted on the stream
@@ -1362,25 +1363,32 @@ static const int kWalkTiles[][3] = {{32, 8, 0},   {64, 8, 0},   {64, 16, 0},  {1
                                     {512, 32, 1}};
 static const int kStoredTiles[][2] = {{64, 8}, {96, 8}, {128, 8}, {96, 16}, {192, 8}, {256, 16}};
 
+// Room for every shape that the tuner may leave in the handle, so that a buffer
+// sized before it is large enough after it.
 static size_t work_bytes_for(const ci_basis* b)
 {
-    size_t w = std::max(vjp_layout(b, b->tune, false).bytes, vjp_layout(b, b->tune, true).bytes);
+    size_t w = 0;
     ci_tuning t = b->tune;
-    t.adj_flush = 0;  // the records need the larger buffer
-    w = std::max(w, std::max(vjp_layout(b, t, false).bytes, vjp_layout(b, t, true).bytes));
-    for (const auto& tl : kWalkTiles) {
-        t.adj_rows = tl[0];
-        t.adj_tile_n = tl[1];
-        t.adj_wide = tl[2];
+    auto walk = [&](int rows, int tile_n, int wide) {
+        t.adj_rows = rows;
+        t.adj_tile_n = tile_n;
+        t.adj_wide = wide;
         w = std::max(w, vjp_layout(b, t, false).bytes);
-    }
-    t = b->tune;
-    t.adj_flush = 0;
-    for (const auto& tl : kStoredTiles) {
-        t.adjk_rows = tl[0];
-        t.adjk_tile_n = tl[1];
+    };
+    auto stored = [&](int rows, int tile_n) {
+        t.adjk_rows = rows;
+        t.adjk_tile_n = tile_n;
         w = std::max(w, vjp_layout(b, t, true).bytes);
-    }
+    };
+    t.adj_flush = 0;  // the records need the larger buffer
+    const ci_tuning &c = b->tune, &u = b->untuned;
+    walk(c.adj_rows, c.adj_tile_n, c.adj_wide);
+    if (u.adj_rows != c.adj_rows || u.adj_tile_n != c.adj_tile_n || u.adj_wide != c.adj_wide)
+        walk(u.adj_rows, u.adj_tile_n, u.adj_wide);
+    for (const auto& tl : kWalkTiles) walk(tl[0], tl[1], tl[2]);
+    stored(c.adjk_rows, c.adjk_tile_n);
+    if (u.adjk_rows != c.adjk_rows || u.adjk_tile_n != c.adjk_tile_n) stored(u.adjk_rows, u.adjk_tile_n);
+    for (const auto& tl : kStoredTiles) stored(tl[0], tl[1]);
     return w;
 }
 
@@ -1504,88 +1512,120 @@ int ci_hamiltonian_tune(ci_basis* b, const float* tbme, const int64_t* row_ptr, 
         return hip_fail(e, "hipEventCreate");
     }
     const ci_tuning start = b->tune;
-    ci_tuning best = start;
+    // The handle's own shapes and the untuned ones are timed with the listed
+    // ones, so that the choice is not slower than not tuning (6Li Nmax = 6: the
+    // untuned 64 x 8 takes 1090 us, the best listed shape 1140; D = 7,916: 120
+    // and 173).  Not below 512 rows, fewer than the workgroups that the device
+    // holds: there one adjoint is mostly launches (D = 59: 35 us untuned, 35 the
+    // best listed; D = 223: 51 and 55, one shape's repeats 51 to 58).
+    std::vector<ci_tuning> own;
+    if (b->nrows >= 512) own = {start, b->untuned};
     int rc = CI_OK;
-    // fill: waves per workgroup x (grid, persistent with several grab sizes)
-    float best_ms = 0.0f;
-    bool have = false;
+    auto fill_ms = [&](const ci_tuning& t) {
+        float ms = 0.0f;
+        rc = time_ms([&] { return launch_fill(b->d_bases, b->rows, tbme, row_ptr, b->n_rowptr, col, val, nullptr, t,
+                                              b->d_queue, 0, s); }, reps, s, e0, e1, &ms);
+        return ms;
+    };
+    auto vjp_ms = [&](const ci_tuning& t, const uint32_t* words) {
+        float ms = 0.0f;
+        rc = time_ms([&] { return vjp_launch(b, row_ptr, grad_val, grad_tbme, work, t, s, words); }, reps, s, e0, e1,
+                     &ms);
+        return ms;
+    };
+    // The fastest of cand, whose first n_own are the handle's own: another one
+    // than these is timed a second time, in turn with the best of them.
+    auto fastest = [&](const std::vector<ci_tuning>& cand, size_t n_own, auto&& time, float* ms) {
+        size_t best = 0, mine = 0;
+        std::vector<float> t(cand.size());
+        for (size_t i = 0; i < cand.size() && rc == CI_OK; i++) {
+            t[i] = time(cand[i]);
+            if (t[i] < t[best]) best = i;
+            if (i < n_own && t[i] < t[mine]) mine = i;
+        }
+        if (rc == CI_OK && n_own > 0 && best != mine) {
+            t[mine] = std::min(t[mine], time(cand[mine]));
+            if (rc == CI_OK) t[best] = std::max(t[best], time(cand[best]));
+            if (t[mine] <= t[best]) best = mine;
+        }
+        *ms = t[best];
+        return cand[best];
+    };
+    // fill: waves per workgroup x (grid, persistent with several grab sizes), and
+    // on its own the grid in XCD-contiguous order
+    std::vector<ci_tuning> cand[2];
+    size_t n_own[2] = {0, 0};
+    for (const ci_tuning& t : own) {
+        cand[t.row_xcd].push_back(t);
+        n_own[t.row_xcd]++;
+    }
     for (int waves : {4, 8})
         for (int grab : {-1, 0, 1, 4, 16}) {  // -1: grid in XCD-contiguous order
-            if (rc != CI_OK) break;
-            b->tune = start;
-            b->tune.row_waves = waves;
-            b->tune.row_grab = grab < 0 ? 0 : grab;
-            b->tune.row_xcd = grab < 0 ? 1 : 0;
-            float ms = 0.0f;
-            rc = time_ms([&] { return launch_fill(b->d_bases, b->rows, tbme, row_ptr, b->n_rowptr, col, val, nullptr, b->tune, b->d_queue, 0,
-                                                  s); },
-                         reps, s, e0, e1, &ms);
-            if (rc == CI_OK && (!have || ms < best_ms)) {
-                best_ms = ms;
-                best.row_waves = waves;
-                best.row_grab = b->tune.row_grab;
-                best.row_xcd = b->tune.row_xcd;
-                have = true;
-            }
+            ci_tuning t = start;
+            t.row_waves = waves;
+            t.row_grab = grab < 0 ? 0 : grab;
+            t.row_xcd = grab < 0 ? 1 : 0;
+            cand[t.row_xcd].push_back(t);
         }
+    float order_ms[2] = {0.0f, 0.0f};
+    ci_tuning by_order[2];
+    for (int x = 0; x < 2; x++) by_order[x] = fastest(cand[x], n_own[x], fill_ms, &order_ms[x]);
     // adjoint that walks the partner lists: tile (rows, neutron width) x (grid, persistent)
-    have = false;
+    auto with_walk = [](ci_tuning t, const ci_tuning& a) {
+        t.adj_rows = a.adj_rows;
+        t.adj_tile_n = a.adj_tile_n;
+        t.adj_wide = a.adj_wide;
+        t.adj_persistent = a.adj_persistent;
+        t.adj_flush = a.adj_flush;
+        return t;
+    };
+    auto walk_ms = [&](const ci_tuning& t) { return vjp_ms(t, nullptr); };
+    std::vector<ci_tuning> walks;
+    for (const ci_tuning& t : own) walks.push_back(with_walk(by_order[0], t));
     for (const auto& tl : kWalkTiles)
         for (int pers : {0, 1})
             for (int flush : {0, 1}) {
-                if (rc != CI_OK) break;
-                b->tune = best;
-                b->tune.adj_rows = tl[0];
-                b->tune.adj_tile_n = tl[1];
-                b->tune.adj_wide = tl[2];
-                b->tune.adj_persistent = pers;
-                b->tune.adj_flush = flush;
-                float ms = 0.0f;
-                rc = time_ms([&] { return vjp_launch(b, row_ptr, grad_val, grad_tbme, work, b->tune, s); }, reps, s, e0,
-                             e1, &ms);
-                if (rc == CI_OK && (!have || ms < best_ms)) {
-                    best_ms = ms;
-                    best.adj_rows = tl[0];
-                    best.adj_tile_n = tl[1];
-                    best.adj_wide = tl[2];
-                    best.adj_persistent = pers;
-                    best.adj_flush = flush;
-                    have = true;
-                }
+                ci_tuning t = by_order[0];
+                t.adj_rows = tl[0];
+                t.adj_tile_n = tl[1];
+                t.adj_wide = tl[2];
+                t.adj_persistent = pers;
+                t.adj_flush = flush;
+                walks.push_back(t);
             }
+    float ms = 0.0f;
+    ci_tuning best = fastest(walks, own.size(), walk_ms, &ms);
+    // the workgroup order belongs to both passes: the other one if their sum is shorter
+    if (rc == CI_OK) {
+        walks = {with_walk(by_order[1], best)};
+        if (start.row_xcd)
+            for (const ci_tuning& t : own) walks.push_back(with_walk(by_order[1], t));
+        float ms1 = 0.0f;
+        const ci_tuning other = fastest(walks, 0, walk_ms, &ms1);
+        if (rc == CI_OK && order_ms[1] + ms1 < order_ms[0] + ms) best = other;
+    }
     // adjoint from stored words (when the caller gives room for them): the
     // fill writes the words once, then its own tiles x (grid, persistent)
     if (keys && rc == CI_OK) {
-        b->tune = best;
         e = launch_fill(b->d_bases, b->rows, tbme, row_ptr, b->n_rowptr, col,
-                        val, keys, b->tune, b->d_queue, 0, s);
+                        val, keys, best, b->d_queue, 0, s);
         if (e != hipSuccess) rc = hip_fail(e, "autotune fill with stored words");
-        have = false;
+        std::vector<ci_tuning> stored;
+        auto add = [&](int rows, int tile_n, int pers) {
+            ci_tuning t = best;
+            t.adjk_rows = rows;
+            t.adjk_tile_n = tile_n;
+            t.adjk_persistent = pers;
+            stored.push_back(t);
+        };
+        for (const ci_tuning& t : own) add(t.adjk_rows, t.adjk_tile_n, t.adjk_persistent);
         for (const auto& tl : kStoredTiles)
-            for (int pers : {0, 1}) {
-                if (rc != CI_OK) break;
-                b->tune = best;
-                b->tune.adjk_rows = tl[0];
-                b->tune.adjk_tile_n = tl[1];
-                b->tune.adjk_persistent = pers;
-                float ms = 0.0f;
-                rc = time_ms([&] { return vjp_launch(b, row_ptr, grad_val, grad_tbme, work, b->tune, s, keys); }, reps,
-                             s, e0, e1, &ms);
-                if (rc == CI_OK && (!have || ms < best_ms)) {
-                    best_ms = ms;
-                    best.adjk_rows = tl[0];
-                    best.adjk_tile_n = tl[1];
-                    best.adjk_persistent = pers;
-                    have = true;
-                }
-            }
+            for (int pers : {0, 1}) add(tl[0], tl[1], pers);
+        best = fastest(stored, own.size(), [&](const ci_tuning& t) { return vjp_ms(t, keys); }, &ms);
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    if (rc != CI_OK) {
-        b->tune = start;
-        return rc;
-    }
+    if (rc != CI_OK) return rc;
     b->tune = best;
     remember_tuning(b->probs, best);
     // leave col / val (/ keys) / grad_tbme as the chosen shapes compute them
