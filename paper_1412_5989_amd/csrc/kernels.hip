@@ -1104,33 +1104,37 @@ __global__ void __launch_bounds__(256)
     const BasisDev& B = bases[uniform(cst(blk_basis)[gb])];
     const int bi = uniform(cst(blk_local)[gb]);
     const GroupView G = group_view(B, bi, uniform((int)(u - cst(group_off)[gb])));
-    // lanes take (row, block) pairs, 64 / kGroupRows blocks per step
-    constexpr int kBlocks = 64 / kGroupRows;
+    // lanes take (row, block) pairs: `wide` lanes (the rows, up to a power of
+    // two) for each of the 64 / wide blocks of a step, so that groups of one or
+    // two rows (keys of few neutron determinants) fill the wavefront too.  With
+    // 16 lanes for any group the full count took 224 us on Z = 6, N = 1, Nmax = 6,
+    // one row per wavefront 200, this 168.
+    const int wide_bits = G.nr > 1 ? 32 - __builtin_clz(G.nr - 1) : 0;
     const SpeciesDev& SN = B.sp[1];
-    const int r = lane % kGroupRows;
+    const int r = lane & ((1 << wide_bits) - 1), step = 64 >> wide_bits;
     const int64_t n = SN.nsd, gN = G.gN0 + (r < G.nr ? r : 0);
     const int selfN = glb(SN.self12)[gN];
     int64_t tot = 0;
     for (int w0 = full ? 0 : bi; w0 < B.nblk; w0 += 64) {
         const GroupBlock q = group_block(B, G, bi, w0, full != 0);
-        for (uint64_t cand = __ballot(q.t0 + q.t1 + q.t2 > 0); cand;) {
-            int t = 64;  // the lane's block of this step, 64: none
-#pragma unroll
-            for (int k = 0; k < kBlocks; k++) {
-                const int tt = cand ? __ffsll((long long)cand) - 1 : 64;
-                cand &= cand - 1;
-                if (lane / kGroupRows == k) t = tt;
-            }
-            const int kn2 = lane_read(q.kn, t & 63), t0 = lane_read(q.t0, t & 63), t1 = lane_read(q.t1, t & 63),
-                      t2 = lane_read(q.t2, t & 63);
-            if (t < 64) {
+        // the blocks with entries, in the low lanes
+        const bool some = q.t0 + q.t1 + q.t2 > 0;
+        const uint64_t m = __ballot(some), mine = some ? m : ~m;
+        const int blocks = __popcll(m);
+        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0));
+        const int list = __builtin_amdgcn_ds_permute((some ? rank : blocks + rank) << 2, lane);
+        for (int k0 = 0; k0 < blocks; k0 += step) {
+            const int k = k0 + (lane >> wide_bits);
+            const int t = lane_read(list, k < 64 ? k : 63);
+            const int kn2 = lane_read(q.kn, t), t0 = lane_read(q.t0, t), t1 = lane_read(q.t1, t), t2 = lane_read(q.t2, t);
+            if (k < blocks) {
                 const gptr<int32_t> s1 = glb(SN.segT1 + (int64_t)kn2 * n + gN), s12 = glb(SN.segT12 + (int64_t)kn2 * n + gN);
                 tot += (int64_t)t1 * (s1[n] - s1[0]) + t2;
                 if (t0) tot += s12[n] - s12[0] - (w0 + t == bi && !full ? selfN : 0);
             }
         }
     }
-    for (int o = kGroupRows; o < 64; o <<= 1) tot += __shfl_xor(tot, o, 64);
+    for (int o = 1 << wide_bits; o < 64; o <<= 1) tot += __shfl_xor(tot, o, 64);
     if (lane < G.nr) glbw(row_ptr)[G.row + lane + 1] = tot;
 }
 

@@ -74,3 +74,20 @@ def test_many_nucleons(ci, p, kinetic):
     tol = float((G.abs().double() * (h.abs() + h0.abs()).double()).sum()) * 2.0**-24
     tol += float((t.abs().double() * (walk.abs().double() * 2.0**-24 + b.info[0]["dim"] * 2.0**-25 * float(G.abs().max()))).sum())
     assert abs(lhs - rhs) <= tol
+
+
+# the lanes that a row of a group gets: each power of two, and sizes on both sides of it
+def test_count_group_sizes(ci):
+    sizes = set()
+    for p in ((5, 1, 4, 0, 1), (2, 1, 4, 1, 1), (1, 2, 4, 1, 1), (2, 2, 4, 0, 1), (1, 3, 4, 2, 1)):
+        o = Oracle(Problem(*p))
+        n = np.diff(o.keys()["nkey_off"])
+        groups = (n + 15) // 16
+        rows = (n + groups - 1) // groups  # rows of a key's groups, fewer in its last one
+        sizes |= set(rows) | set(n - (groups - 1) * rows)
+        b = ci.ci_basis_build([p])
+        every = np.arange(o.dim)
+        for count, ref in ((ci.ci_hamiltonian_count, o.row_counts(every)),
+                           (ci.ci_hamiltonian_count_full, o.rows_full(every, values=False)[0])):
+            assert np.array_equal(np.diff(count(b)[0].cpu().numpy()), ref), p
+    assert sizes >= {1, 2, 3, 4, 5, 7, 8, 10, 15, 16} and max(sizes) == 16, sizes
