@@ -352,8 +352,8 @@ __global__ void __launch_bounds__(256) partner_decode(PartnerArgs A, int64_t n1,
 
 // Segment counts -> segment offsets (exclusive scan over the keys of each
 // determinant x), in both orders: seg[x][key], read by a wavefront that works
-// on one x, and segT[key][x], read by one that works on neighbouring x in one
-// key.  List lengths into l*_ptr[x + 1].  A workgroup takes kOffDets
+// on one x, and segT[key][x] (null: not wanted), read by one that works on
+// neighbouring x in one key.  List lengths into l*_ptr[x + 1].  A workgroup takes kOffDets
 // determinants of one of the two lists, a wavefront a quarter of them, lanes
 // take keys; the transposed copy goes through LDS so that its stores are
 // contiguous too.
@@ -387,6 +387,7 @@ __global__ void __launch_bounds__(64 * kPartnerWaves) partner_offsets(PartnerArg
             if (x0 + i < nsd && k0 + lane <= nk) seg[(int64_t)(x0 + i) * (nk + 1) + k0 + lane] = off;
             run[i] += __shfl(incl, 63, 64);
         }
+        if (!segT) continue;
         __syncthreads();
         const int m = nk + 1 - k0 < 64 ? nk + 1 - k0 : 64;
         for (int t = threadIdx.x; t < m * kOffDets; t += 64 * kPartnerWaves) {

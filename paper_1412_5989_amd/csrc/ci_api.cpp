@@ -227,6 +227,7 @@ void fill_info(const HostBasis& hb, ci_basis_info& in)
 // offsets of one species' tables in the arena
 struct SpOff {
     size_t sd, sd_key, key_off, key_nq, key_m2, kmap, l1_ptr, l12_ptr, seg1, seg12, segT1, segT12, self12;
+    // (segT1, segT12: 0 for a table that is no problem's neutrons)
 };
 struct UOff {
     SpOff sp[2];
@@ -488,6 +489,7 @@ struct BuildPlan {
     std::vector<std::shared_ptr<HostBasis>> ub;
     std::unique_ptr<PairIndexer> pairs;  // two-body pair indexes, on a helper thread
     std::vector<int> canon;
+    std::vector<char> as_neutrons;  // species table 2u + s is the neutrons of some problem
     std::vector<UOff> uo;
     size_t pair_start = 0, host_bytes = 0;
     size_t o_row = 0, o_group = 0, o_first = 0, o_last = 0, o_blk_basis = 0, o_blk_local = 0;
@@ -548,6 +550,8 @@ int plan_build(const ci_problem* probs, int32_t n_probs, BuildPlan& P, std::stri
                 break;
             }
     }
+    P.as_neutrons.assign(nsp, 0);
+    for (int i = 1; i < nsp; i += 2) P.as_neutrons[P.canon[i]] = 1;
     // Arena: tables the host writes first (mirrored and copied up), then the
     // tables the device computes (never copied).
     Layout L;
@@ -611,8 +615,10 @@ int plan_build(const ci_problem* probs, int32_t n_probs, BuildPlan& P, std::stri
             o.l12_ptr = L.take<int64_t>(nsd + 1);
             o.seg1 = L.take<int32_t>(nsd * (nk + 1));
             o.seg12 = L.take<int32_t>(nsd * (nk + 1));
-            o.segT1 = L.take<int32_t>(nsd * (nk + 1));
-            o.segT12 = L.take<int32_t>(nsd * (nk + 1));
+            if (P.as_neutrons[c]) {  // the count reads the transposed tables of neutrons only
+                o.segT1 = L.take<int32_t>(nsd * (nk + 1));
+                o.segT12 = L.take<int32_t>(nsd * (nk + 1));
+            }
             o.self12 = L.take<int32_t>(nsd);
             ubytes[u] += L.off - s0;
             max_scan = std::max<int64_t>(max_scan, (int64_t)nsd + 1);
@@ -651,8 +657,8 @@ PartnerArgs partner_args(const ci_basis& h, size_t u, int sidx)
     a.l12_ptr = (int64_t*)(dev + o.l12_ptr);
     a.seg1 = (int32_t*)(dev + o.seg1);
     a.seg12 = (int32_t*)(dev + o.seg12);
-    a.segT1 = (int32_t*)(dev + o.segT1);
-    a.segT12 = (int32_t*)(dev + o.segT12);
+    a.segT1 = o.segT1 ? (int32_t*)(dev + o.segT1) : nullptr;
+    a.segT12 = o.segT12 ? (int32_t*)(dev + o.segT12) : nullptr;
     a.self12 = (int32_t*)(dev + o.self12);
     a.orb_qn = (const int32_t*)(dev + h.uo[u].orb_qn);
     a.kmap = (const int32_t*)(dev + o.kmap);
@@ -906,8 +912,8 @@ int ci_basis_build(const ci_problem* probs, int32_t n_probs, ci_basis_info* info
             sd.l12_ptr = (const int64_t*)D(o.l12_ptr);
             sd.seg1 = (const int32_t*)D(o.seg1);
             sd.seg12 = (const int32_t*)D(o.seg12);
-            sd.segT1 = (const int32_t*)D(o.segT1);
-            sd.segT12 = (const int32_t*)D(o.segT12);
+            sd.segT1 = o.segT1 ? (const int32_t*)D(o.segT1) : nullptr;
+            sd.segT12 = o.segT12 ? (const int32_t*)D(o.segT12) : nullptr;
             sd.self12 = (const int32_t*)D(o.self12);
             sd.nsd = (int32_t)hb.sp[sidx].nsd();
             sd.nk = hb.sp[sidx].nk();

@@ -58,8 +58,8 @@ struct SpeciesDev {
     const uint64_t* l12;     // d<=2 partners in keys of the same 2M and Nq parity
     const int32_t* seg1;     // [nsd][nk + 1] first record of each key in l1(x)
     const int32_t* seg12;    // [nsd][nk + 1] same for l12(x)
-    const int32_t* segT1;    // [nk + 1][nsd] seg1 transposed
-    const int32_t* segT12;   // [nk + 1][nsd] seg12 transposed
+    const int32_t* segT1;    // [nk + 1][nsd] seg1 transposed (neutrons; may be null for protons)
+    const int32_t* segT12;   // [nk + 1][nsd] seg12 transposed (as segT1)
     const int32_t* self12;   // [nsd] position of x itself inside its own key segment of l12(x)
     int32_t nsd, nk;
 };
@@ -181,7 +181,7 @@ struct PartnerArgs {
     uint64_t* l12;
     int32_t* seg1;  // [nsd][nk + 1]
     int32_t* seg12;
-    int32_t* segT1;  // [nk + 1][nsd]
+    int32_t* segT1;  // [nk + 1][nsd], null for a table that is no problem's neutrons
     int32_t* segT12;
     int32_t* self12;
     const int32_t* orb_qn;   // [nsps] n | l << 8 | 2j << 16 | (2m + 64) << 24 of each orbit

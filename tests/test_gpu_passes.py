@@ -91,3 +91,16 @@ def test_count_group_sizes(ci):
                            (ci.ci_hamiltonian_count_full, o.rows_full(every, values=False)[0])):
             assert np.array_equal(np.diff(count(b)[0].cpu().numpy()), ref), p
     assert sizes >= {1, 2, 3, 4, 5, 7, 8, 10, 15, 16} and max(sizes) == 16, sizes
+
+
+# one determinant table as the neutrons of one problem and the protons of another
+@pytest.mark.parametrize("ps", [[(1, 4, 2, 1, -1), (4, 1, 2, 1, -1)], [(4, 1, 2, 1, -1), (1, 4, 2, 1, -1)],
+                                [(4, 1, 2, 1, -1)], [(4, 0, 4, 0, 1), (2, 4, 2, 0, 1)]])
+def test_count_of_shared_species(ci, ps):
+    b = ci.ci_basis_build(ps)
+    for k, p in enumerate(ps):
+        o = Oracle(Problem(*p))
+        rows = np.arange(o.dim)
+        for count, ref in ((ci.ci_hamiltonian_count, o.row_counts(rows)),
+                           (ci.ci_hamiltonian_count_full, o.rows_full(rows, values=False)[0])):
+            assert np.array_equal(np.diff(b.row_ptr_slice(count(b)[0], k).cpu().numpy()), ref), p

@@ -223,3 +223,15 @@ def test_coefficient_routine_of_the_decoupling_tables_is_exact_enough():
     assert ci.ci_clebsch_gordan(1, 1, 1, 1, 4, 2) == 0.0  # outside the triangle
     with pytest.raises(ci.CIError):
         ci.ci_clebsch_gordan(121, 1, 1, 1, 120, 2)
+
+
+def test_arena_holds_transposed_segments_of_neutrons_only():
+    # [n_sd][n_keys + 1] int32 twice: the same problem with protons and neutrons
+    # exchanged differs by these tables of the two species
+    a, b = ci.ci_basis_plan([(1, 5, 6, 0, 1)])[0], ci.ci_basis_plan([(5, 1, 6, 0, 1)])[0]
+    assert (a["n_psd"], a["n_pkeys"]) == (b["n_nsd"], b["n_nkeys"])
+    tables = [2 * 4 * i["n_nsd"] * (i["n_nkeys"] + 1) for i in (a, b)]
+    assert abs((a["arena_bytes"] - b["arena_bytes"]) - (tables[0] - tables[1])) < 4096
+    # one species table that is the neutrons of one problem of a batch and the protons of another
+    c = ci.ci_basis_plan([(1, 5, 6, 0, 1), (5, 1, 6, 0, 1)])[0]
+    assert c["arena_bytes"] < a["arena_bytes"] + b["arena_bytes"]
