@@ -75,10 +75,18 @@ class EventTimer:
         return float(np.mean([a.elapsed_time(b) for a, b in self.pairs])) if self.pairs else 0.0
 
 
-def measured_counters(profile: str):
+# launch shapes that a kernel's counters depend on
+FILL_SHAPE = ("row_waves", "row_grab", "row_xcd")
+ADJ_SHAPE = ("adj_rows", "adj_tile_n", "adj_persistent", "row_xcd", "adj_wide", "adj_flush")
+ADJK_SHAPE = ("adjk_rows", "adjk_tile_n", "adjk_persistent", "row_xcd", "adj_flush")
+
+
+def measured_counters(profile: str, shape=None):
     """Per-launch figures from a committed counter summary under profiles/
     (lines "name: value"), or None when the kernel source named in it has
-    changed since the counters were taken (its SHA-256 no longer matches)."""
+    changed since the counters were taken (its SHA-256 no longer matches), or
+    when they were taken at other launch shapes than `shape` (a dict; the
+    summary names its own as launch_shape: name=value,...)."""
     path = os.path.join(ROOT, "profiles", profile)
     if not os.path.exists(path):
         return None
@@ -96,6 +104,10 @@ def measured_counters(profile: str):
         return None
     if fields.get("kernel_source_sha256") != digest:
         return None
+    if shape is not None:
+        taken = dict(kv.split("=") for kv in fields.get("launch_shape", "").split(",") if kv)
+        if any(taken.get(k) != str(v) for k, v in shape.items()):
+            return None
     out = {}
     for k in ("traffic_bytes_per_launch", "valu_insts_per_launch"):
         if k in fields:
@@ -432,7 +444,8 @@ def run_batched(ci, torch, steps, warmup, stored, tuning_text=None):
     alg = 12 * tot + 16 * (dim_total + len(probs)) + 4 * b.n_tbme
     achieved = alg / (ms * 1e-3) / 1e9
     # traffic of one replay: the committed counter summaries of its two kernels
-    cf, ca = measured_counters("row_kernel_fill_batch64.md"), measured_counters("adjoint_kernel_batch64.md")
+    cf = measured_counters("row_kernel_fill_batch64.md", {k: tuning[k] for k in FILL_SHAPE})
+    ca = measured_counters("adjoint_kernel_batch64.md", {k: tuning[k] for k in ADJ_SHAPE})
     traffic = (cf["traffic_bytes_per_launch"] + ca["traffic_bytes_per_launch"]) if (cf and ca and not stored) else None
     out = {"bases": len(probs), "dim_total": dim_total, "nnz_total": tot, "n_tbme_total": b.n_tbme,
            "ms_per_replay": ms, "nnz_per_s": tot / (ms * 1e-3), "setup_s": t_setup,
@@ -450,11 +463,12 @@ def run_batched(ci, torch, steps, warmup, stored, tuning_text=None):
 VALU_PEAK = 256 * 4 * 2.4e9 / 4
 
 
-def leg(ms, nnz, alg_bytes, profile):
+def leg(ms, nnz, alg_bytes, profile, shape):
     """nonzeros/s, the HBM roofline of the leg's kernel from its algorithmic
     bytes, and the VALU issue fraction from the committed counters of that
-    kernel (null when its source changed since they were taken)."""
-    c = measured_counters(profile) if profile else None
+    kernel (null when its source changed since they were taken, or when they
+    were taken at other launch shapes)."""
+    c = measured_counters(profile, shape) if profile else None
     achieved = alg_bytes / (ms * 1e-3) / 1e9
     out = {"ms": ms, "nnz_per_s": nnz / (ms * 1e-3),
            "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -577,9 +591,9 @@ def measure_step(ci, torch, workload, steps, warmup, adjoint, tuning_text):
     fill_alg = 8 * nnz + 8 * (D + 1)
     vjp_alg = 4 * nnz + 8 * (D + 1) + 4 * n_tbme
     fwd = leg(fill_ms, nnz, fill_alg, ("row_kernel_fill_keys_%s.md" if stored else "row_kernel_fill_%s.md")
-              % workload)
+              % workload, {k: tuning[k] for k in FILL_SHAPE})
     adj = leg(vjp_ms, nnz, vjp_alg, ("adjoint_stored_kernel_%s.md" if stored else "adjoint_kernel_%s.md")
-              % workload)
+              % workload, {k: tuning[k] for k in (ADJK_SHAPE if stored else ADJ_SHAPE)})
     return {"prob": prob, "dim": D, "nnz": nnz, "n_tbme": n_tbme, "sec": sec, "tuning": tuning,
             "tune_s": t_tune, "fixed": fixed is not None,
             "stages_ms": {"basis_build": 1e3 * float(np.mean(t_basis)),
