@@ -115,7 +115,12 @@ typedef struct {
 typedef struct ci_basis ci_basis; /* opaque */
 
 /* Launch shapes of the fill and of the adjoint, kept in
- * the handle.  Every shape computes the same result; only the time differs.
+ * the handle.  Every shape of the fill computes the same bits; the adjoint's
+ * tile shapes differ by the rounding that ci_hamiltonian_vjp states.  Untuned
+ * shapes follow from the total rows of the handle and, from 65,536 rows on,
+ * from how full its tiles are, so the gradient of one basis may round
+ * differently beside other bases of a batch than alone; equal shapes set by
+ * hand give equal bits.
  * The fill takes one row per wavefront: either a grid that covers every
  * row once (row_grab = 0), or a persistent grid (as many workgroups as the
  * device holds at once) whose wavefronts take row_grab consecutive rows at a
@@ -218,8 +223,8 @@ int ci_hamiltonian_vjp(const ci_basis* b, const int64_t* row_ptr, const float* g
  * ci_hamiltonian_fill_keys writes what ci_hamiltonian_fill writes (the same
  * col and val bits) and also keys (device uint32, one word per stored entry,
  * same positions): for an entry that is one two-body term, its position in
- * the basis' table (low 30 bits; all ones when no table element exists) and
- * its sign (bit 30); for the diagonal and one-nucleon differences (several
+ * the basis' table (low 30 bits; all ones, which the fill does not write, for
+ * no term) and its sign (bit 30); for the diagonal and one-nucleon differences (several
  * terms, Sec. 2), bit 31 and a record of the moved nucleon.  The words are
  * opaque to the caller and valid for this handle and row_ptr only.
  * ci_hamiltonian_vjp_keys computes what ci_hamiltonian_vjp computes from

@@ -382,11 +382,20 @@ int64_t count_tiles_of(const HostBasis& hb, const ci_tuning& t, bool stored)
 // 15,764 106 -> 107, 36,779 224 -> 207, 48,917 255 -> 251, 139,816 967 -> 851,
 // 186,894 1147 -> 1090, 288,930 1261 -> 1089, 581,740 2772 -> 2153.  (96 rows
 // would take 2065 there, but the fixed-point grid coarsens with the rows.)
+// Around the borders (24 x 8 / 32 x 16 / 64 x 8, same table): D = 11,870 84 / 81
+// / 75, 13,162 139 / 135 / 180, 15,764 124 / 143 / 175, 17,040 137 / 141 / 180,
+// 27,852 146 / 187 / 220, 45,166 299 / 316 / 293, 51,355 262 / 258 / 316, 73,426
+// 332 / 359 / 384, 87,007 416 / 417 / 408, 111,832 617 / 576 / 497, 157,486 1108 /
+// 1078 / 901: near 16,384 rows the first two differ by less than the bases do,
+// and 64 rows pay from about 90,000.
 // The adjoint from stored words keeps 16384 slots and one workgroup per CU
 // (8192 and two: 899 -> 1062 us at D = 186,894; it is bound by the atomics).
 // Measured (us; 96 x 8 rows, persistent -> the shape below): D = 15,764 114 ->
 // 91, 48,917 233 -> 194, 186,894 903 (96 x 8), 288,930 934 -> 875, 581,740
-// 1708 -> 1582.
+// 1708 -> 1582.  Around the borders (64 x 16 grid / 96 x 8 and 128 x 16
+// persistent): D = 51,355 204 / 230 / 272, 73,426 277 / 287 / 325, 87,007 318 /
+// 322 / 350, 111,832 457 / 421 / 421, 157,486 850 / 785 / 791, 239,096 820 / 723 /
+// 735.
 // From 65,536 rows on, a basis whose blocks hold few proton determinants leaves
 // 64 x 8 tiles mostly empty: below 32 rows per tile on average the neutron
 // width is 32, on a persistent grid (the same 64 rows, so the same fixed-point

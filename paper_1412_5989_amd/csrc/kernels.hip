@@ -15,14 +15,14 @@
 //   2. lanes take 64 segments (target block, P') at a time and compute each
 //      segment's number of entries from the neutron partner lists of N
 //      (a wave scan gives each segment's first output position);
-//   3. lanes take 64 consecutive entries at a time, find their segment by a
-//      binary search in LDS, and write col/val: consecutive lanes write
+//   3. lanes take 64 consecutive entries at a time, find their segment by
+//      marks in LDS (owner_of), and write col/val: consecutive lanes write
 //      consecutive addresses.
 // Entries that differ in two nucleons are one signed two-body element and are
-// finished in step 3.  The diagonal and one-nucleon differences are sums of
-// many elements; they are queued in LDS and evaluated term-parallel (one lane
-// per two-body term, a segmented wave reduction in a fixed order), so a long
-// sum never stalls the other 63 lanes.
+// finished in step 3.  One-nucleon differences are sums of many elements; they
+// are queued in LDS and evaluated with one lane per two-body term (summed in a
+// fixed order), so a long sum never stalls the other 63 lanes.  The diagonal
+// entry, one pair per lane, comes last.
 //
 // The same walk serves the fill pass and the adjoint (step 3 scatters phase *
 // upstream value onto the table).  The count pass needs no walk: the number of
@@ -291,9 +291,11 @@ __device__ __forceinline__ uint64_t lane_read64(uint64_t v, int l)
 }
 
 // Word stored per entry for the adjoint: a single two-body term holds its
-// table position in the low 30 bits (kKeyNone: no table element, the entry is
-// 0) and its sign in bit 30; a multi-term entry (diagonal, one nucleon moved)
-// sets bit 31 and holds its queue record in the low 25 bits.
+// table position in the low 30 bits and its sign in bit 30; a multi-term entry
+// (diagonal, one nucleon moved) sets bit 31 and holds its queue record in the
+// low 25 bits.  kKeyNone is no position (the tables are smaller) and the fill
+// never writes it, as every pair that two basis states hold is in the table;
+// the adjoint passes over it.
 constexpr uint32_t kKeySpecial = 0x80000000u;
 constexpr uint32_t kKeyNeg = 0x40000000u;
 constexpr uint32_t kKeyPos = 0x3fffffffu;
@@ -325,8 +327,8 @@ struct RowView {
 // Adjoint contribution g to table position k of the row's basis, in fixed
 // point: q = rint(g * 2^qshift), an exact power-of-two scaling and one
 // rounding.  Integer sums do not depend on their order, so the gradient is the
-// same bit for bit whatever the tile shape, the flush and the order in which
-// wavefronts and atomics meet.  The shift is chosen from max |G| and the rows
+// same bit for bit whatever the flush and the order in which wavefronts and
+// atomics meet, and for all tiles of one shift.  The shift is chosen from max |G| and the rows
 // of a tile so that a tile's sum in an int32 LDS slot cannot overflow: a row
 // adds at most one contribution to any table position (its moves are distinct
 // and a move and its reverse cannot both start from one determinant), so a slot
