@@ -25,6 +25,7 @@ on a bounded sample of rows.
 from __future__ import annotations
 
 import argparse
+import glob
 import hashlib
 import json
 import os
@@ -468,7 +469,13 @@ def leg(ms, nnz, alg_bytes, profile, shape):
     bytes, and the VALU issue fraction from the committed counters of that
     kernel (null when its source changed since they were taken, or when they
     were taken at other launch shapes)."""
-    c = measured_counters(profile, shape) if profile else None
+    # the kernel's summaries: <profile>.md, and <profile>_<tiles>.md at other launch shapes
+    c = None
+    for path in sorted(glob.glob(os.path.join(ROOT, "profiles", profile[:-3] + "*.md"))):
+        c = measured_counters(os.path.basename(path), shape)
+        if c:
+            profile = os.path.basename(path)
+            break
     achieved = alg_bytes / (ms * 1e-3) / 1e9
     out = {"ms": ms, "nnz_per_s": nnz / (ms * 1e-3),
            "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -41,3 +41,12 @@ def test_other_or_no_shape(profile, shape):
 def test_other_source(profile):
     profile("launch_shape: adj_rows=64,adj_tile_n=8\n").write_text("other")
     assert bench.measured_counters("p.md", SHAPE) is None
+
+
+def test_leg_finds_the_summary_of_its_shape(profile, tmp_path):
+    profile("launch_shape: adj_rows=64,adj_tile_n=8\n")
+    other = (tmp_path / "profiles" / "p.md").read_text().replace("launch: 7", "launch: 9").replace("=64", "=96")
+    (tmp_path / "profiles" / "p_96x8.md").write_text(other)
+    for rows, traffic, name in ((64, 7, "p.md"), (96, 9, "p_96x8.md"), (32, None, None)):
+        r = bench.leg(1.0, 1, 8, "p.md", {"adj_rows": rows, "adj_tile_n": 8})["roofline"]
+        assert (r["traffic"], r["profile"]) == (traffic, name)
